@@ -1183,6 +1183,18 @@ static int attn_stream_qt(int64_t L) {
     return 2;
 }
 
+// Key splits of the FP32 attention kernels, on 32-key blocks: enough for
+// `target` groups of four waves over `groups` of them per split, but at least
+// four key blocks each (a split of fewer costs more in the launch that joins
+// the splits: 128 heads of 128 14.6 us with one split, 21.5 with two; one
+// head of 64 10.2 against 12.3).
+void attn_f32_splits(int64_t L, int64_t groups, int64_t target, int64_t* splits, int64_t* kps) {
+    const int64_t kblocks = (L + 31) / 32;
+    const int64_t n = std::min<int64_t>((target + groups - 1) / groups, (kblocks + 3) / 4);
+    *kps = (kblocks + n - 1) / n * 32;
+    *splits = (L + *kps - 1) / *kps;
+}
+
 qx_status plan_attn(Plan* pl, int32_t dt, int64_t L, int64_t d, int32_t bound, int32_t route) {
     qx_status st = check_dims({{"L", L}, {"d", d}});
     if (st) return st;
@@ -1282,14 +1294,22 @@ qx_status plan_attn(Plan* pl, int32_t dt, int64_t L, int64_t d, int32_t bound, i
         a.qt = qt;
         LaunchRec rec;
         if (r == R_ATTN_F32_MFMA) {
-            build_attn_f32(a, &rec);
-            rec.bind(offsetof(AttnParams, Q), BIND_IN0);
-            rec.bind(offsetof(AttnParams, K), BIND_IN1);
-            rec.bind(offsetof(AttnParams, V), BIND_IN2);
-            rec.bind(offsetof(AttnParams, O), BIND_OUT);
+            SdpaParams sp{};
+            const int qw = attn_f32_queries(1, L, d);
+            // one workgroup per CU: two waves per SIMD with 256 queries, one with
+            // 128 (two there, of half the keys, cost more partials than they gain)
+            attn_f32_splits(L, (L + qw - 1) / qw * (qw / 128), 2 * qw, &splits, &kps);
+            sp.L = (int32_t)L; sp.d = (int32_t)d; sp.BH = 1;
+            sp.splits = (int32_t)splits; sp.keys_per_split = (int32_t)kps;
+            if (!build_attn_b3(sp, false, &rec))
+                return fail(QX_ERR_UNSUPPORTED, "no attention kernel for d = %lld", (long long)d);
+            rec.bind(offsetof(SdpaParams, Q), BIND_IN0);
+            rec.bind(offsetof(SdpaParams, K), BIND_IN1);
+            rec.bind(offsetof(SdpaParams, V), BIND_IN2);
+            rec.bind(offsetof(SdpaParams, O), BIND_OUT);
             if (splits > 1) {
                 ws = 4 * (uint64_t)splits * (uint64_t)L * (uint64_t)d;
-                rec.bind(offsetof(AttnParams, part), BIND_WS, 0);
+                rec.bind(offsetof(SdpaParams, part), BIND_WS, 0);
                 pl->launches.push_back(rec);
                 ReduceParams rp{};
                 rp.n = L * d;
@@ -1398,20 +1418,18 @@ qx_status plan_sdpa(Plan* pl, int64_t BH, int64_t L, int64_t d, float scale, int
         info.workspace_bytes = 0;
         return QX_OK;
     }
-    // Key splits only while the query blocks of all heads leave the chip
-    // short of 512 workgroups; split boundaries on 32-key blocks.
-    const int64_t wgs = (L + 127) / 128 * BH;
-    const int64_t kblocks = (L + 31) / 32;
-    int64_t splits = std::min<int64_t>(std::max<int64_t>((512 + wgs - 1) / wgs, 1), kblocks);
-    const int64_t kps = ((kblocks + splits - 1) / splits) * 32;
-    splits = (L + kps - 1) / kps;
+    // Key splits only while the query blocks of all heads leave the chip short
+    // of 512 groups of four waves (two per SIMD).
+    const int qw = attn_f32_queries(BH, L, d);
+    int64_t splits, kps;
+    attn_f32_splits(L, (L + qw - 1) / qw * (qw / 128) * BH, 512, &splits, &kps);
     SdpaParams a{};
     a.L = (int32_t)L; a.d = (int32_t)d; a.BH = (int32_t)BH;
     a.splits = (int32_t)splits; a.keys_per_split = (int32_t)kps;
     a.causal = causal;
     a.c = (float)((double)scale * 1.4426950408889634);   // log2(e)
     LaunchRec rec;
-    if (!build_sdpa_f32(a, &rec)) return fail(QX_ERR_UNSUPPORTED, "no attention kernel for d = %lld", (long long)d);
+    if (!build_attn_b3(a, true, &rec)) return fail(QX_ERR_UNSUPPORTED, "no attention kernel for d = %lld", (long long)d);
     rec.bind(offsetof(SdpaParams, Q), BIND_IN0);
     rec.bind(offsetof(SdpaParams, K), BIND_IN1);
     rec.bind(offsetof(SdpaParams, V), BIND_IN2);
@@ -1436,7 +1454,7 @@ qx_status plan_sdpa(Plan* pl, int64_t BH, int64_t L, int64_t d, float scale, int
     } else {
         pl->launches.push_back(rec);
     }
-    info.tile_m = 128; info.tile_n = (int32_t)d; info.tile_k = (int32_t)kps;
+    info.tile_m = qw; info.tile_n = (int32_t)d; info.tile_k = (int32_t)kps;
     info.kernels = (int32_t)pl->launches.size();
     info.workspace_bytes = (int64_t)ws;
     return QX_OK;

@@ -1,16 +1,18 @@
 // k_attn.hip -- the single-head attention core O = (Q K^T) V on matrix cores
 // (Methodology: attention operator of the form O = (Q K^T) V; Table 2,
-// attention rows).  No scale, softmax or mask.
+// attention rows), without scale, softmax or mask, and the FP32 softmax form
+// (the attention baseline of Table 2's footnote).
 //
-// Both kernels keep S on chip.  A wave owns 32 queries; per block of 32 keys
+// All kernels keep S on chip.  A wave owns 32 queries; per block of 32 keys
 // it forms S^T = K_blk Q^T with one MFMA chain, whose 32x32 accumulator
 // (lane = query, 16 registers = 16 keys) is exactly the A operand layout of
 // the second product O += S V once the V operand is gathered with the same
 // key permutation (the order of a contraction's terms is free).  Keys are
 // split across workgroups; partial results are combined in a fixed order.
 //
-//  * FP32: v_mfma_f32_32x32x2f32 for both products; per-split partials are
-//    reduced in split order, so repeated runs are bit-identical.
+//  * FP32: operands as three bf16 terms on v_mfma_f32_32x32x16_bf16, six
+//    products kept (k_attn_b3, which also is the softmax attention); per-split
+//    partials are reduced in split order, so repeated runs are bit-identical.
 //  * INT32 (|q|,|k|,|v| <= 127 and d*max^2 < 2^23): S^T on
 //    v_mfma_i32_32x32x32_i8; every S is read as three offset int8 limbs,
 //    S = s0 + 2^8 s1 + 2^16 s2 + 32896, where the limbs are the bytes of
@@ -23,6 +25,7 @@ namespace qx {
 
 typedef float f16x __attribute__((ext_vector_type(16)));
 typedef float f4 __attribute__((ext_vector_type(4)));
+typedef float f4u __attribute__((ext_vector_type(4), aligned(4)));   // a caller's output may be 4-byte aligned
 typedef int i16x __attribute__((ext_vector_type(16)));
 typedef int i4 __attribute__((ext_vector_type(4)));
 
@@ -31,102 +34,15 @@ constexpr int AQW = 32;      // queries per wave
 constexpr int AQ = 4 * AQW;  // queries per workgroup
 constexpr int AKB = 32;      // keys per block
 
-// ---------------------------------------------------------------------------
-// FP32
-// ---------------------------------------------------------------------------
-template <int D>
-__global__ __launch_bounds__(AT) void k_attn_f32(const AttnParams p) {
-    constexpr int DP = D + 4;            // padded LDS row (floats)
-    constexpr int HALF = D / 2;          // K-slot h of a 32x32x2 MFMA covers d-half h
-    constexpr int NTO = D / 32;          // output column tiles
-    constexpr int LD4 = AKB * D / 4 / AT;  // float4 loads per thread per operand
-    __shared__ float Ks[AKB][DP];
-    __shared__ float Vs[AKB][DP];
-
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, h = lane >> 5, l32 = lane & 31;
-    const int q0 = blockIdx.x * AQ + wave * AQW;
-    const int split = blockIdx.y;
-    const int key_lo = split * p.keys_per_split;
-    const int key_hi = min(p.L, key_lo + p.keys_per_split);
-    const float* Q = (const float*)p.Q;
-    const float* Kp = (const float*)p.K;
-    const float* Vp = (const float*)p.V;
-
-    float qf[HALF];
-    {
-        const int q = q0 + l32;
-#pragma unroll
-        for (int t = 0; t < HALF; t += 4) {
-            f4 v = (q < p.L) ? *(const f4*)(Q + (int64_t)q * D + HALF * h + t) : f4{};
-            qf[t] = v[0]; qf[t + 1] = v[1]; qf[t + 2] = v[2]; qf[t + 3] = v[3];
-        }
-    }
-    f16x o[NTO];
-#pragma unroll
-    for (int n = 0; n < NTO; ++n) o[n] = f16x{};
-
-    f4 rk[LD4], rv[LD4];
-    auto load = [&](int kb) {
-#pragma unroll
-        for (int i = 0; i < LD4; ++i) {
-            const int v = tid + AT * i, row = v / (D / 4), c4 = v % (D / 4);
-            const int key = kb + row;
-            const bool in = key < key_hi;
-            rk[i] = in ? *(const f4*)(Kp + (int64_t)key * D + c4 * 4) : f4{};
-            rv[i] = in ? *(const f4*)(Vp + (int64_t)key * D + c4 * 4) : f4{};
-        }
-    };
-    auto stash = [&]() {
-#pragma unroll
-        for (int i = 0; i < LD4; ++i) {
-            const int v = tid + AT * i, row = v / (D / 4), c4 = v % (D / 4);
-            *(f4*)&Ks[row][c4 * 4] = rk[i];
-            *(f4*)&Vs[row][c4 * 4] = rv[i];
-        }
-    };
-
-    if (key_lo < key_hi) load(key_lo);
-    for (int kb = key_lo; kb < key_hi; kb += AKB) {
-        __syncthreads();              // previous block fully consumed
-        stash();
-        __syncthreads();
-        if (kb + AKB < key_hi) load(kb + AKB);
-        // S^T[key][query] = sum_t K[key][t] Q[query][t]
-        f16x s = f16x{};
-#pragma unroll
-        for (int t = 0; t < HALF; t += 4) {
-            const f4 kv = *(const f4*)&Ks[l32][HALF * h + t];
-#pragma unroll
-            for (int e = 0; e < 4; ++e)
-                s = __builtin_amdgcn_mfma_f32_32x32x2f32(kv[e], qf[t + e], s, 0, 0, 0);
-        }
-        // O[query][c] += sum_key S[query][key] V[key][c]; register r of lane
-        // half h holds key 8*(r/4) + 4*h + r%4.
-#pragma unroll
-        for (int r = 0; r < 16; ++r) {
-            const int key = 8 * (r >> 2) + 4 * h + (r & 3);
-#pragma unroll
-            for (int n = 0; n < NTO; ++n)
-                o[n] = __builtin_amdgcn_mfma_f32_32x32x2f32(s[r], Vs[key][n * 32 + l32], o[n], 0, 0, 0);
-        }
-    }
-
-    float* dst = p.splits > 1 ? (float*)p.part + (int64_t)split * p.L * D : (float*)p.O;
-#pragma unroll
-    for (int n = 0; n < NTO; ++n)
-#pragma unroll
-        for (int r = 0; r < 16; ++r) {
-            const int q = q0 + 8 * (r >> 2) + 4 * h + (r & 3);
-            if (q < p.L) dst[(int64_t)q * D + n * 32 + l32] = o[n][r];
-        }
-}
-
+// Sum of the key splits' partials in split order, four outputs a thread
+// (n is a multiple of 32).
 __global__ __launch_bounds__(AT) void k_reduce_splits(const ReduceParams p) {
-    const int64_t i = (int64_t)blockIdx.x * AT + threadIdx.x;
+    const int64_t i = ((int64_t)blockIdx.x * AT + threadIdx.x) * 4;
     if (i >= p.n) return;
-    float s = p.part[i];
-    for (int k = 1; k < p.splits; ++k) s += p.part[(int64_t)k * p.n + i];
-    p.out[i] = s;
+    f4 s = *(const f4*)(p.part + i);
+#pragma unroll 4
+    for (int k = 1; k < p.splits; ++k) s += *(const f4*)(p.part + (int64_t)k * p.n + i);
+    *(f4u*)(p.out + i) = s;
 }
 
 // ---------------------------------------------------------------------------
@@ -736,72 +652,159 @@ __global__ __launch_bounds__(512) void k_attn_i32s(const AttnParams p) {
 }
 
 // ---------------------------------------------------------------------------
-// Softmax attention, FP32, BH heads (the SDPA-with-softmax form of the
-// attention baseline, Table 2 footnote; the attention core with a softmax,
-// Discussion).  Same S^T = K_blk Q^T layout as k_attn_f32: lane (query l32,
-// half h) holds 16 of the 32 scores of its query in a key block.  Per block
-// the running maximum m (base-2 exponent domain, t = scale*log2(e)*s) and the
-// running sum are updated online; the exponentials are the A operand of
-// O += P V, and O's rows (registers, not lanes) are rescaled by the factor of
-// their query, fetched from the lane that owns it.  With key splits every
-// split writes unnormalised O, its maximum and its sum; k_sdpa_combine merges
-// them in split order, so repeated runs are bit-identical.
+// FP32 on the bf16 matrix cores.  A float of 24 significant bits is the exact
+// sum of three bf16 values, x = h + m + l with |m| <= 2^-9 |x| and
+// |l| <= 2^-18 |x| (each the rounding of what the ones before it leave).  A
+// product keeps the six terms down to 2^-18 of it (l l, l m and m l, below
+// 2^-26, are under the fp32 rounding), summed in the MFMA's fp32 accumulator,
+// smallest terms first.  Six v_mfma_f32_32x32x16_bf16 (32 cycles each, 16 k)
+// replace eight v_mfma_f32_32x32x2f32 (64 cycles each): 192 against 512
+// cycles.  The error is no larger: one such step over 16 products rounds to
+// 0.41 ulp rms of the running sum where eight fp32 steps gave 0.92 to 1.16
+// (measured), and its mean is 0 as theirs.
+//
+// The split is exact, and no product overflows, for x = 0 or
+// LO <= |x| < HI; SplitRange notes a value outside (infinities and NaN among
+// them), and the block it lies in is contracted on the fp32 matrix cores
+// instead, from the caller's arrays.
+// ---------------------------------------------------------------------------
+typedef __bf16 b8 __attribute__((ext_vector_type(8)));
+typedef __bf16 b2 __attribute__((ext_vector_type(2)));
+typedef float f2 __attribute__((ext_vector_type(2)));
+
+// eight floats -> their three bf16 terms
+__device__ __forceinline__ void split3(const float (&x)[8], b8& h, b8& m, b8& l) {
+    uint32_t hw[4], mw[4], lw[4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        const float x0 = x[2 * i], x1 = x[2 * i + 1];
+        hw[i] = __builtin_bit_cast(uint32_t, __builtin_convertvector(f2{x0, x1}, b2));
+        const float r0 = x0 - __uint_as_float(hw[i] << 16), r1 = x1 - __uint_as_float(hw[i] & 0xFFFF0000u);
+        mw[i] = __builtin_bit_cast(uint32_t, __builtin_convertvector(f2{r0, r1}, b2));
+        const float s0 = r0 - __uint_as_float(mw[i] << 16), s1 = r1 - __uint_as_float(mw[i] & 0xFFFF0000u);
+        lw[i] = __builtin_bit_cast(uint32_t, __builtin_convertvector(f2{s0, s1}, b2));
+    }
+    h = __builtin_bit_cast(b8, hw);
+    m = __builtin_bit_cast(b8, mw);
+    l = __builtin_bit_cast(b8, lw);
+}
+
+// Tracks whether every value seen is 0 or has 2^ELO <= |x| < 2^EHI.
+template <int ELO, int EHI>
+struct SplitRange {
+    uint32_t lo = 0xFFFFFFFFu, hi = 0u;
+    __device__ __forceinline__ void see(float x) {
+        const uint32_t u = __float_as_uint(x) << 1;   // sign dropped
+        hi = max(hi, u);
+        lo = min(lo, u - 1u);                         // 0 wraps to the largest
+    }
+    __device__ __forceinline__ bool bad() const {
+        return hi >= (uint32_t)(EHI + 127) << 24 || lo < ((uint32_t)(ELO + 127) << 24) - 1u;
+    }
+};
+
+// ---------------------------------------------------------------------------
+// Attention on split operands: the core O = (Q K^T) V (SM = false) and the
+// softmax form (SM = true).  NW waves of 32 queries; blocks of 32 keys are
+// split once per workgroup while they are staged: K planes by key (rows of D),
+// V planes transposed (a column's 32 keys, in the order in which the lanes
+// hold S).  S^T = K Q^T leaves lane (query l32, half h) with keys
+// 8*(r/4) + 4*h + r%4 of register r; split again, those registers are the B
+// operand of O^T += V^T S^T, so O stays by query too and the softmax's factors
+// never change lanes.  One barrier per block; a block's loads are in flight
+// for a whole block before it is staged.
+//
+// Bound: the matrix cores' power.  16 heads x 4096 x 64, softmax: 344 us
+// (590 us on v_mfma_f32_32x32x2f32), matrix cores busy 65% of the cycles at
+// 1.74 GHz; per 32x32 block and wave 1536 matrix cycles against about 1250 of
+// vector ALU (exponentials, splits).  Without the software pipeline (PIPE,
+// which d >= 96 has no registers for: d = 128 measured 237 us with it and
+// spills, 200 without) the two waves of a SIMD meet in their vector phases:
+// 363 us, 51% busy.  The core at L = 4096, d = 64: 36 us (40 us before).
+//
+// Softmax: per block the running maximum m (base-2 exponent domain,
+// t = scale*log2(e)*s) and the running sum are updated online.  With key
+// splits every split writes unnormalised O, its maximum and its sum;
+// k_sdpa_combine merges them in split order (the core: k_reduce_splits adds
+// the partials in split order), so repeated runs are bit-identical.
 // RAG: d < D, columns d..D-1 read as zeros and are not written.
 // ---------------------------------------------------------------------------
-template <int D, bool RAG>
-__global__ __launch_bounds__(AT) void k_sdpa_f32(const SdpaParams p) {
-    constexpr int DP = D + 4;
-    constexpr int HALF = D / 2;
-    constexpr int NTO = D / 32;
-    constexpr int LD4 = AKB * D / 4 / AT;
-    // two LDS buffers: block j is staged into buffer j&1 while the other
-    // holds block j-1, so one barrier per block suffices
-    __shared__ float Ksb[2][AKB][DP];
-    __shared__ float Vsb[2][AKB][DP];
+template <int D, int NW, bool SM, bool RAG>
+__global__ __launch_bounds__(NW * 64) void k_attn_b3(const SdpaParams p) {
+    constexpr int NTH = NW * 64;
+    constexpr int QW = 32 * NW;              // queries per workgroup
+    constexpr int KS = D / 16;               // 16-k steps of Q K^T
+    constexpr int NTO = D / 32;              // output row tiles of O^T
+    constexpr int KP = 2 * D + 16;           // bytes of a K row and of a V column in LDS (padded:
+    constexpr int VP = 2 * AKB + 16;         // 16 rows of one chunk fall on 64 different banks)
+    constexpr int KB = AKB * KP, VB = D * VP;            // bytes of one plane
+    constexpr int NI = (8 * D + NTH - 1) / NTH;          // staging items (8 elements) per thread
+    constexpr bool PIPE = D <= 64;
+    // products of the core reach |q k| d |v| L: its values are held closer to 1
+    typedef SplitRange<SM ? -100 : -40, SM ? 60 : 30> Range;
+    __shared__ __align__(16) unsigned char lds[2][3 * (KB + VB)];
+    __shared__ int out_of_range;
 
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, h = lane >> 5, l32 = lane & 31;
+    const int tid = threadIdx.x, lane = tid & 63, h = lane >> 5, l32 = lane & 31;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), wave64 = wave * 64;
     // Under the mask a query block's work grows with its index: the dispatch
     // order (x fastest, then z) hands out the longest blocks of every head
     // first, so that the short ones fill in behind them.
     int qblk = blockIdx.x;
     int64_t head = blockIdx.z;
-    if (p.causal) {
+    if (SM && p.causal) {
         const int id = (int)blockIdx.x + (int)gridDim.x * (int)blockIdx.z;
         qblk = (int)gridDim.x - 1 - id / (int)gridDim.z;
         head = id % (int)gridDim.z;
     }
-    const int qb = qblk * AQ;
+    const bool causal = SM && p.causal;
+    const int qb = qblk * QW;
     const int q0 = qb + wave * AQW;
     const int split = blockIdx.y;
     const int d = RAG ? p.d : D;
     const int key_lo = split * p.keys_per_split;
     int key_hi = min(p.L, key_lo + p.keys_per_split);
-    if (p.causal) key_hi = min(key_hi, qb + AQ);
+    if (causal) key_hi = min(key_hi, qb + QW);
     const int64_t hoff = head * p.L * d;
     const float* Q = p.Q + hoff;
     const float* Kp = p.K + hoff;
     const float* Vp = p.V + hoff;
 
-    auto ld4 = [&](const float* base, int row, int c4) -> f4 {
-        if (!RAG) return *(const f4*)(base + (int64_t)row * D + c4 * 4);
-        f4 v;
+    // eight elements c8.. of the row that starts at base + row; past d they
+    // read as the row's last element (zero: as 0)
+    auto ld8 = [&](const float* base, unsigned row, int c8, bool zero, float (&v)[8]) {
+        const float* src = base + row;
+        if (!RAG || c8 + 8 <= d) {
+            const f4u a = *(const f4u*)(src + c8), b = *(const f4u*)(src + c8 + 4);
 #pragma unroll
-        for (int e = 0; e < 4; ++e) {
-            const int col = c4 * 4 + e;
-            v[e] = col < d ? base[(int64_t)row * d + col] : 0.f;
+            for (int e = 0; e < 4; ++e) { v[e] = a[e]; v[4 + e] = b[e]; }
+        } else {
+#pragma unroll
+            for (int e = 0; e < 8; ++e) {
+                v[e] = src[min(c8 + e, d - 1)];
+                if (zero && c8 + e >= d) v[e] = 0.f;
+            }
         }
-        return v;
     };
 
-    const int q = q0 + l32;           // this lane's query in the S^T layout
-    // Q is taken pre-multiplied by c = scale*log2(e), so the scores come out
-    // of the MFMAs already in the base-2 exponent domain.
-    const float c = p.c;
-    float qf[HALF];
+    const int q = q0 + l32;           // this lane's query
+    // Softmax: Q is taken pre-multiplied by c = scale*log2(e), so the scores
+    // come out of the MFMAs already in the base-2 exponent domain.
+    const float c = SM ? p.c : 1.f;
+    b8 qh[KS], qm[KS], ql[KS];        // k-slot (h, e) of step t is d-index 16 t + 8 h + e
+    Range rg;                         // of every value this thread splits
+    {
 #pragma unroll
-    for (int t = 0; t < HALF; t += 4) {
-        const f4 v = q < p.L ? ld4(Q, q, (HALF * h + t) / 4) : f4{};
-        qf[t] = v[0] * c; qf[t + 1] = v[1] * c; qf[t + 2] = v[2] * c; qf[t + 3] = v[3] * c;
+        for (int t = 0; t < KS; ++t) {
+            float v[8] = {};
+            if (q < p.L) ld8(Q, (unsigned)q * d, 16 * t + 8 * h, true, v);
+#pragma unroll
+            for (int e = 0; e < 8; ++e) {
+                v[e] *= c;
+                rg.see(v[e]);
+            }
+            split3(v, qh[t], qm[t], ql[t]);
+        }
     }
     f16x o[NTO];
 #pragma unroll
@@ -809,66 +812,118 @@ __global__ __launch_bounds__(AT) void k_sdpa_f32(const SdpaParams p) {
     float m = -INFINITY;              // running maximum of t for query q
     float lsum = 0.f;                 // this half's share of the running sum
 
-    f4 rk[LD4], rv[LD4];
-    auto load = [&](int kb) {
+    const int nblk = max(0, (key_hi - key_lo + AKB - 1) / AKB);
+    // blocks this wave contracts: under the mask, those with a key at or before its last query
+    const int nact = causal ? max(0, min(nblk, (q0 + 2 * AQW - 1 - key_lo) / AKB)) : nblk;
+    // Staging items: 4 D of K (row, eight columns), then 4 D of V (column,
+    // eight keys); 4 D is a multiple of 64, so a wave's items are of one kind.
+    // Keys past key_hi read as the last key and columns past d as the last
+    // column, so no load is guarded: the scores of such keys are masked, Q is
+    // 0 in such columns and O's are not written.
+    typedef float Stage[NI][8];
+    auto load = [&](Stage& st, int jk, int jv) {
+        const int kk = key_lo + min(jk, nblk - 1) * AKB, kv = key_lo + min(jv, nblk - 1) * AKB;
+        const float* Kb = Kp + (int64_t)kk * d;
+        const float* Vb = Vp + (int64_t)kv * d;
+        const int last_k = key_hi - 1 - kk, last_v = key_hi - 1 - kv;
 #pragma unroll
-        for (int i = 0; i < LD4; ++i) {
-            const int v = tid + AT * i, row = v / (D / 4), c4 = v % (D / 4);
-            const int key = kb + row;
-            const bool in = key < key_hi;
-            rk[i] = in ? ld4(Kp, key, c4) : f4{};
-            rv[i] = in ? ld4(Vp, key, c4) : f4{};
+        for (int i = 0; i < NI; ++i) {
+            const int iw = wave64 + NTH * i, it = iw + lane;
+            if (NI * NTH != 8 * D && iw >= 8 * D) break;
+            if (iw < 4 * D) {
+                ld8(Kb, (unsigned)(min(it / (D / 8), last_k) * d), it % (D / 8) * 8, false, st[i]);
+            } else {
+                const int iv = it - 4 * D, sh = iv / D, k0 = 16 * (sh >> 1) + 4 * (sh & 1);
+                const unsigned col = RAG ? min(iv % D, d - 1) : iv % D;
+                if (last_v >= AKB - 1) {
+                    const float* src = Vb + (k0 * d + col);
+#pragma unroll
+                    for (int e = 0; e < 8; ++e) st[i][e] = src[(8 * (e >> 2) + (e & 3)) * d];
+                } else {
+#pragma unroll
+                    for (int e = 0; e < 8; ++e)
+                        st[i][e] = Vb[(unsigned)min(k0 + 8 * (e >> 2) + (e & 3), last_v) * d + col];
+                }
+            }
         }
     };
-    auto stash = [&](int buf) {
+    // block jk of K into buffer jk & 1 and block jv of V into buffer jv & 1
+    auto stash = [&](const Stage& st, int jk, int jv) {
 #pragma unroll
-        for (int i = 0; i < LD4; ++i) {
-            const int v = tid + AT * i, row = v / (D / 4), c4 = v % (D / 4);
-            *(f4*)&Ksb[buf][row][c4 * 4] = rk[i];
-            *(f4*)&Vsb[buf][row][c4 * 4] = rv[i];
+        for (int i = 0; i < NI; ++i) {
+            const int iw = wave64 + NTH * i, it = iw + lane, iv = it - 4 * D;
+            if (NI * NTH != 8 * D && iw >= 8 * D) break;
+            const bool is_k = iw < 4 * D;
+#pragma unroll
+            for (int e = 0; e < 8; ++e) rg.see(st[i][e]);
+            b8 a, b, l;
+            split3(st[i], a, b, l);
+            unsigned char* dst = is_k ? &lds[jk & 1][(it / (D / 8)) * KP + it % (D / 8) * 16]
+                                      : &lds[jv & 1][3 * KB + (iv % D) * VP + iv / D * 16];
+            const int plane = is_k ? KB : VB;
+            *(b8*)dst = a;
+            *(b8*)(dst + plane) = b;
+            *(b8*)(dst + 2 * plane) = l;
         }
     };
-
-    if (key_lo < key_hi) load(key_lo);
-    int buf = 0;
-    for (int kb = key_lo; kb < key_hi; kb += AKB, buf ^= 1) {
-        // Buffer buf was last read two blocks ago: every wave finished that
-        // block before the previous iteration's barrier.
-        stash(buf);
-        __syncthreads();
-        if (kb + AKB < key_hi) load(kb + AKB);
-        float (&Ks)[AKB][DP] = Ksb[buf];
-        float (&Vs)[AKB][DP] = Vsb[buf];
-        if (p.causal && kb > q0 + AQW - 1) continue;   // every key after every query of this wave
-        f16x s = f16x{};
+    // S^T of block j
+    auto scores = [&](int j, f16x& s) {
+        const unsigned char* Ks = &lds[j & 1][l32 * KP + 16 * h];
+        s = f16x{};
 #pragma unroll
-        for (int t = 0; t < HALF; t += 4) {
-            const f4 kv = *(const f4*)&Ks[l32][HALF * h + t];
-#pragma unroll
-            for (int e = 0; e < 4; ++e)
-                s = __builtin_amdgcn_mfma_f32_32x32x2f32(kv[e], qf[t + e], s, 0, 0, 0);
+        for (int t = 0; t < KS; ++t) {
+            const b8 kh = *(const b8*)(Ks + 32 * t), km = *(const b8*)(Ks + KB + 32 * t),
+                     kl = *(const b8*)(Ks + 2 * KB + 32 * t);
+            s = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kl, qh[t], s, 0, 0, 0);
+            s = __builtin_amdgcn_mfma_f32_32x32x16_bf16(km, qm[t], s, 0, 0, 0);
+            s = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kh, ql[t], s, 0, 0, 0);
+            s = __builtin_amdgcn_mfma_f32_32x32x16_bf16(km, qh[t], s, 0, 0, 0);
+            s = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kh, qm[t], s, 0, 0, 0);
+            s = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kh, qh[t], s, 0, 0, 0);
         }
-        // Register r holds key kb + 8*(r/4) + 4*h + r%4.  In a block that
-        // reaches past key_hi or (causal) past a query of this wave, keys at
-        // or past key_lim are set to -inf, whose exponential is 0.
-        if (kb + AKB > key_hi || (p.causal && kb + AKB - 1 > q0)) {
-            const int key_lim = p.causal ? min(key_hi, q + 1) : key_hi;
+    };
+    auto scores_f32 = [&](int j, f16x& s) {
+        const int key = key_lo + j * AKB + l32;
+        s = f16x{};
+#pragma unroll 1
+        for (int t = 0; t < D; t += 16) {
+            float kv[8] = {}, qv[8] = {};
+            if (key < key_hi) ld8(Kp, (unsigned)key * d, t + 8 * h, true, kv);
+            if (q < p.L) ld8(Q, (unsigned)q * d, t + 8 * h, true, qv);
+#pragma unroll
+            for (int e = 0; e < 8; ++e)
+                s = __builtin_amdgcn_mfma_f32_32x32x2f32(kv[e], qv[e] * c, s, 0, 0, 0);
+        }
+    };
+    // Register r holds key kb + 8*(r/4) + 4*h + r%4.  In a block that
+    // reaches past key_hi or (causal) past a query of this wave, keys at or
+    // past key_lim are set to -inf, whose exponential is 0, or (no softmax)
+    // to 0.
+    auto mask = [&](int j, f16x& s) {
+        const int kb = key_lo + j * AKB;
+        if (kb + AKB > key_hi || (causal && kb + AKB - 1 > q0)) {
+            const int key_lim = causal ? min(key_hi, q + 1) : key_hi;
             const int kl = key_lim - kb - 4 * h;    // register r is kept iff 8*(r/4) + r%4 < kl
 #pragma unroll
             for (int r = 0; r < 16; ++r)
-                if (8 * (r >> 2) + (r & 3) >= kl) s[r] = -INFINITY;
+                if (8 * (r >> 2) + (r & 3) >= kl) s[r] = SM ? -INFINITY : 0.f;
         }
+    };
+    float alpha = 1.f, m_use = 0.f;   // the next block's rescale factor and subtracted maximum
+    auto maximum = [&](const f16x& s) {
         float mx = fmaxf(fmaxf(s[0], s[1]), s[2]);
 #pragma unroll
         for (int r = 3; r < 15; r += 2) mx = fmaxf(fmaxf(mx, s[r]), s[r + 1]);
         mx = fmaxf(mx, s[15]);
         mx = fmaxf(mx, __shfl_xor(mx, 32));
         const float m_new = fmaxf(m, mx);
-        const float m_use = m_new == -INFINITY ? 0.f : m_new;
+        m_use = m_new == -INFINITY ? 0.f : m_new;
         // v_exp_f32 directly: arguments are <= 0 here, results below 2^-126
         // flush to 0, which no sum of a row with its maximum term 1 can see
-        const float alpha = __builtin_amdgcn_exp2f(m - m_use);
+        alpha = __builtin_amdgcn_exp2f(m - m_use);
         m = m_new;
+    };
+    auto exponentials = [&](f16x& s) {
         float ps = 0.f;
 #pragma unroll
         for (int r = 0; r < 16; ++r) {
@@ -876,55 +931,189 @@ __global__ __launch_bounds__(AT) void k_sdpa_f32(const SdpaParams p) {
             ps += s[r];
         }
         lsum = lsum * alpha + ps;
-        if (__ballot(alpha != 1.f) != 0) {
-            // row r of O is query 8*(r/4) + 4*h + r%4, whose factor lane that index holds
+    };
+    auto split_s = [&](const f16x& s, b8 (&ph)[2], b8 (&pm)[2], b8 (&pl)[2]) {
 #pragma unroll
-            for (int r = 0; r < 16; ++r) {
-                const float a = __shfl(alpha, 8 * (r >> 2) + 4 * h + (r & 3));
+        for (int t = 0; t < 2; ++t) {
+            float pv[8];
 #pragma unroll
-                for (int n = 0; n < NTO; ++n) o[n][r] *= a;
-            }
+            for (int e = 0; e < 8; ++e) pv[e] = s[8 * t + e];
+            split3(pv, ph[t], pm[t], pl[t]);
         }
+    };
+    // O^T += V^T S^T of block j; consecutive products go to different tiles
+    auto accumulate = [&](int j, const b8 (&ph)[2], const b8 (&pm)[2], const b8 (&pl)[2]) {
+        const unsigned char* Vs = &lds[j & 1][3 * KB + l32 * VP + 16 * h];
+#pragma unroll
+        for (int t = 0; t < 2; ++t) {
+            b8 vh[NTO], vm[NTO], vl[NTO];
+#pragma unroll
+            for (int n = 0; n < NTO; ++n) {
+                const unsigned char* src = Vs + n * 32 * VP + 32 * t;
+                vh[n] = *(const b8*)src;
+                vm[n] = *(const b8*)(src + VB);
+                vl[n] = *(const b8*)(src + 2 * VB);
+            }
+#define QX_PV(V_, P_) \
+            _Pragma("unroll") for (int n = 0; n < NTO; ++n) \
+                o[n] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(V_[n], P_[t], o[n], 0, 0, 0);
+            QX_PV(vl, ph) QX_PV(vm, pm) QX_PV(vh, pl) QX_PV(vm, ph) QX_PV(vh, pm) QX_PV(vh, ph)
+#undef QX_PV
+        }
+    };
+    auto accumulate_f32 = [&](int j, const f16x& s) {
 #pragma unroll
         for (int r = 0; r < 16; ++r) {
-            const int key = 8 * (r >> 2) + 4 * h + (r & 3);
-#pragma unroll
-            for (int n = 0; n < NTO; ++n)
-                o[n] = __builtin_amdgcn_mfma_f32_32x32x2f32(s[r], Vs[key][n * 32 + l32], o[n], 0, 0, 0);
-        }
-    }
-
-    const float l = lsum + __shfl_xor(lsum, 32);
-    const int64_t rows = (int64_t)p.BH * p.L;
-    if (p.splits > 1) {
-        float* part = p.part + ((int64_t)split * rows + head * p.L) * d;
-#pragma unroll
-        for (int n = 0; n < NTO; ++n)
-#pragma unroll
-            for (int r = 0; r < 16; ++r) {
-                const int qr = q0 + 8 * (r >> 2) + 4 * h + (r & 3), col = n * 32 + l32;
-                if (qr < p.L && (!RAG || col < d)) part[(int64_t)qr * d + col] = o[n][r];
-            }
-        if (h == 0 && q < p.L) {
-            float* st = p.stat + ((int64_t)split * rows + head * p.L + q) * 2;
-            st[0] = m;
-            st[1] = l;
-        }
-    } else {
-        const float inv = l > 0.f ? 1.f / l : 0.f;
-        float* O = p.O + hoff;
-#pragma unroll
-        for (int r = 0; r < 16; ++r) {
-            const int qi = 8 * (r >> 2) + 4 * h + (r & 3);
-            const float f = __shfl(inv, qi);
-            const int qr = q0 + qi;
+            const int key = key_lo + j * AKB + 8 * (r >> 2) + 4 * h + (r & 3);
 #pragma unroll
             for (int n = 0; n < NTO; ++n) {
                 const int col = n * 32 + l32;
-                if (qr < p.L && (!RAG || col < d)) O[(int64_t)qr * d + col] = o[n][r] * f;
+                const float v = key < key_hi && (!RAG || col < d) ? Vp[(int64_t)key * d + col] : 0.f;
+                o[n] = __builtin_amdgcn_mfma_f32_32x32x2f32(v, s[r], o[n], 0, 0, 0);
             }
         }
+    };
+
+    // Software pipeline: pass j splits the exponentials of block j beside the
+    // score products of block j + 1, then stages K of block j + 2 and V of
+    // block j + 1 beside the O products of block j, so each of the vector
+    // ALU's parts runs under matrix products that do not wait for it.  (The
+    // last pass's scores are of a stale block and are not used.)
+    float m_out = -INFINITY;                 // the maximum that lsum and o are relative to
+    Stage st;
+    auto pass = [&](int j, f16x& s, f16x& sn) {
+        if (!PIPE) {
+            if (j < nact) {
+                scores(j, s);
+                mask(j, s);
+                if (SM) {
+                    maximum(s);
+                    if (__ballot(alpha != 1.f) != 0) {
+#pragma unroll
+                        for (int n = 0; n < NTO; ++n)
+#pragma unroll
+                            for (int r = 0; r < 16; ++r) o[n][r] *= alpha;
+                    }
+                    exponentials(s);
+                }
+                b8 ph[2], pm[2], pl[2];
+                split_s(s, ph, pm, pl);
+                accumulate(j, ph, pm, pl);
+            }
+            stash(st, j + 1, j + 1);
+            load(st, j + 2, j + 2);
+            __syncthreads();
+            return;
+        }
+        if (j < nact) {
+            if (SM && __ballot(alpha != 1.f) != 0) {
+#pragma unroll
+                for (int n = 0; n < NTO; ++n)
+#pragma unroll
+                    for (int r = 0; r < 16; ++r) o[n][r] *= alpha;
+            }
+            m_out = m;
+            b8 ph[2], pm[2], pl[2];
+            scores(j + 1, sn);
+            if (SM) exponentials(s);
+            split_s(s, ph, pm, pl);
+            // all of it before the mask's branch, beside the scores
+#pragma unroll
+            for (int t = 0; t < 2; ++t) asm volatile("" : "+v"(ph[t]), "+v"(pm[t]), "+v"(pl[t]));
+            mask(j + 1, sn);
+            accumulate(j, ph, pm, pl);
+            if (SM) maximum(sn);
+            stash(st, j + 2, j + 1);
+        } else {
+            stash(st, j + 2, j + 1);
+        }
+        load(st, j + 3, j + 2);
+        __syncthreads();
+    };
+    f16x s0 = f16x{}, s1 = f16x{};
+    if (nblk > 0) {
+        load(st, 0, 0);
+        if (PIPE) {
+            Stage st1;
+            load(st1, 1, 1);
+            stash(st, 0, 0);
+            stash(st1, 1, 1);
+            load(st, 2, 1);
+        } else {
+            stash(st, 0, 0);
+            load(st, 1, 1);
+        }
+        __syncthreads();
+        if (PIPE) {
+            if (nact > 0) {
+                scores(0, s0);
+                mask(0, s0);
+                if (SM) maximum(s0);
+            }
+            __syncthreads();                 // pass 0 stages over K of block 0
+        }
+        for (int j = 0; j < nblk; j += 2) {
+            pass(j, s0, s1);
+            if (j + 1 < nblk) pass(j + 1, s1, s0);
+        }
+        if (!PIPE) m_out = m;
     }
+    if (tid == 0) out_of_range = 0;
+    __syncthreads();
+    if (rg.bad()) out_of_range = 1;
+    __syncthreads();
+    if (out_of_range) {
+        // the workgroup starts again on the fp32 matrix cores, each wave by itself
+#pragma unroll
+        for (int n = 0; n < NTO; ++n) o[n] = f16x{};
+        m = m_out = -INFINITY;
+        lsum = 0.f;
+        for (int j = 0; j < nact; ++j) {
+            f16x s;
+            scores_f32(j, s);
+            mask(j, s);
+            if (SM) {
+                maximum(s);
+                m_out = m;
+#pragma unroll
+                for (int n = 0; n < NTO; ++n)
+#pragma unroll
+                    for (int r = 0; r < 16; ++r) o[n][r] *= alpha;
+                exponentials(s);
+            }
+            accumulate_f32(j, s);
+        }
+    }
+
+    // lane (q, h), register r of tile n: column 32 n + 8*(r/4) + 4*h + r%4
+    const float l = SM ? lsum + __shfl_xor(lsum, 32) : 1.f;
+    float f = 1.f;
+    float* dst = p.O + hoff;
+    if (p.splits > 1) {
+        const int64_t rows = (int64_t)p.BH * p.L;
+        dst = p.part + ((int64_t)split * rows + head * p.L) * d;
+        if (SM && h == 0 && q < p.L) {
+            float* stt = p.stat + ((int64_t)split * rows + head * p.L + q) * 2;
+            stt[0] = m_out;
+            stt[1] = l;
+        }
+    } else if (SM) {
+        f = l > 0.f ? 1.f / l : 0.f;
+    }
+    if (q >= p.L) return;
+    dst += (int64_t)q * d;
+#pragma unroll
+    for (int n = 0; n < NTO; ++n)
+#pragma unroll
+        for (int r = 0; r < 16; r += 4) {
+            const int col = 32 * n + 8 * (r >> 2) + 4 * h;
+            const f4 v = f4{o[n][r] * f, o[n][r + 1] * f, o[n][r + 2] * f, o[n][r + 3] * f};
+            if (!RAG) *(f4u*)(dst + col) = v;
+            else
+#pragma unroll
+                for (int e = 0; e < 4; ++e)
+                    if (col + e < d) dst[col + e] = v[e];
+        }
 }
 
 // Merge of the key splits, one thread per output element, splits in order:
@@ -948,21 +1137,6 @@ __global__ __launch_bounds__(AT) void k_sdpa_combine(const SdpaCombineParams p) 
 // ---------------------------------------------------------------------------
 // Builders
 // ---------------------------------------------------------------------------
-bool build_attn_f32(const AttnParams& p, LaunchRec* rec) {
-    switch (p.d) {
-    case 32: rec->fn = (const void*)k_attn_f32<32>; break;
-    case 64: rec->fn = (const void*)k_attn_f32<64>; break;
-    case 96: rec->fn = (const void*)k_attn_f32<96>; break;
-    case 128: rec->fn = (const void*)k_attn_f32<128>; break;
-    default: return false;
-    }
-    rec->name = "attn_f32";
-    rec->grid = dim3((unsigned)((p.L + AQ - 1) / AQ), (unsigned)p.splits, 1);
-    rec->block = dim3(AT, 1, 1);
-    rec->set_params(p);
-    return true;
-}
-
 bool build_attn_i32(const AttnParams& p, LaunchRec* rec) {
     switch (p.d) {
     case 32: rec->fn = (const void*)k_attn_i32<32>; break;
@@ -1028,28 +1202,43 @@ bool build_attn_i32s(const AttnParams& p, LaunchRec* rec) {
 
 void build_reduce(const ReduceParams& p, LaunchRec* rec) {
     rec->fn = (const void*)k_reduce_splits;
-    rec->grid = dim3((unsigned)((p.n + AT - 1) / AT), 1, 1);
+    rec->grid = dim3((unsigned)((p.n / 4 + AT - 1) / AT), 1, 1);
     rec->block = dim3(AT, 1, 1);
     rec->name = "reduce_splits";
     rec->set_params(p);
 }
 
-bool build_sdpa_f32(const SdpaParams& p, LaunchRec* rec) {
+// 256 queries per workgroup share one split of every key block; 128 where
+// that would leave the chip short of workgroups (the core at L = 4096, d = 64
+// 36.4 us with 128 against 38.0, L = 2000, d = 96 27.7 against 33.1; above the
+// line, L = 4096, d = 128 59 us with 256 against 66, 16 softmax heads of
+// 4096 x 64 344 against 375) or more than a fifth of the rows empty (128 causal
+// heads of 128 13.2 against 14.6).
+int attn_f32_queries(int64_t BH, int64_t L, int64_t d) {
+    return BH * L * d > (1 << 18) && (L + 255) / 256 * 256 * 4 <= 5 * L ? 256 : 128;
+}
+
+template <int D, bool SM>
+static const void* attn_b3_fn(int queries, bool rag) {
+    if (queries == 256) return rag ? (const void*)k_attn_b3<D, 8, SM, SM> : (const void*)k_attn_b3<D, 8, SM, false>;
+    return rag ? (const void*)k_attn_b3<D, 4, SM, SM> : (const void*)k_attn_b3<D, 4, SM, false>;
+}
+
+bool build_attn_b3(const SdpaParams& p, bool softmax, LaunchRec* rec) {
     const int D = (p.d + 31) / 32 * 32;
     const bool rag = p.d != D;
-#define QX_SDPA_CASE(DD) \
-    case DD: rec->fn = rag ? (const void*)k_sdpa_f32<DD, true> : (const void*)k_sdpa_f32<DD, false>; break;
+    const int queries = attn_f32_queries(p.BH, p.L, p.d);
+    if (rag && !softmax) return false;
     switch (D) {
-    QX_SDPA_CASE(32)
-    QX_SDPA_CASE(64)
-    QX_SDPA_CASE(96)
-    QX_SDPA_CASE(128)
+    case 32: rec->fn = softmax ? attn_b3_fn<32, true>(queries, rag) : attn_b3_fn<32, false>(queries, rag); break;
+    case 64: rec->fn = softmax ? attn_b3_fn<64, true>(queries, rag) : attn_b3_fn<64, false>(queries, rag); break;
+    case 96: rec->fn = softmax ? attn_b3_fn<96, true>(queries, rag) : attn_b3_fn<96, false>(queries, rag); break;
+    case 128: rec->fn = softmax ? attn_b3_fn<128, true>(queries, rag) : attn_b3_fn<128, false>(queries, rag); break;
     default: return false;
     }
-#undef QX_SDPA_CASE
-    rec->name = "sdpa_f32";
-    rec->grid = dim3((unsigned)((p.L + AQ - 1) / AQ), (unsigned)p.splits, (unsigned)p.BH);
-    rec->block = dim3(AT, 1, 1);
+    rec->name = softmax ? "sdpa_f32" : "attn_f32";
+    rec->grid = dim3((unsigned)((p.L + queries - 1) / queries), (unsigned)p.splits, (unsigned)p.BH);
+    rec->block = dim3((unsigned)(2 * queries), 1, 1);
     rec->set_params(p);
     return true;
 }

@@ -172,13 +172,12 @@ struct ConvDirectParams {
     ConvGeom g;
 };
 
-// Attention core O = (Q K^T) V.
+// INT32 attention core O = (Q K^T) V.
 struct AttnParams {
     const void* Q;
     const void* K;
     const void* V;
     void* O;
-    void* part;             // F32: split partials [splits][L][d] float
     int32_t L, d;
     int32_t splits;         // key splits
     int32_t keys_per_split;
@@ -198,7 +197,8 @@ struct AttnParams {
     int64_t prep_q;         // prep work items: 16-byte Q8 chunks (0: none)
 };
 
-// Softmax attention over BH heads (FP32): O = softmax(scale Q K^T [mask]) V.
+// FP32 attention over BH heads: O = softmax(scale Q K^T [mask]) V, or the core
+// O = (Q K^T) V (BH 1, no scale or mask; only L, d and the splits are read).
 struct SdpaParams {
     const float* Q;         // [BH][L][d]
     const float* K;
@@ -366,7 +366,6 @@ int sums_slices(int K);
 void build_im2col(const Im2colParams& p, LaunchRec* rec);
 void build_valu_gemm(int32_t kind, const ValuGemmParams& p, int batch, LaunchRec* rec);
 void build_valu_skinny_s24(const ValuGemmParams& p, int batch, LaunchRec* rec);   // N of a few tens
-bool build_attn_f32(const AttnParams& p, LaunchRec* rec);
 bool build_attn_i32(const AttnParams& p, LaunchRec* rec);
 // INT32 attention with resident key splits: applicable for d in {32, 64, 128}
 // and splits of kps keys with kps * d a multiple of 4096 and 2 * kps * d <= 48 KiB
@@ -377,7 +376,10 @@ bool build_attn_i32r(const AttnParams& p, LaunchRec* rec);
 // d in {32, 64}, keys_per_split a multiple of 128, V8 block-major
 bool build_attn_i32s(const AttnParams& p, LaunchRec* rec);
 void build_reduce(const ReduceParams& p, LaunchRec* rec);
-bool build_sdpa_f32(const SdpaParams& p, LaunchRec* rec);
+// FP32 attention (the core, d in {32, 64, 96, 128}, or softmax, d <= 128) and
+// the queries per workgroup it takes
+int attn_f32_queries(int64_t BH, int64_t L, int64_t d);
+bool build_attn_b3(const SdpaParams& p, bool softmax, LaunchRec* rec);
 void build_sdpa_combine(const SdpaCombineParams& p, LaunchRec* rec);
 void build_fill(const FillParams& p, LaunchRec* rec);
 void build_range(const RangeParams& p, LaunchRec* rec);

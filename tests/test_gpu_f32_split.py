@@ -1,0 +1,124 @@
+"""FP32 kernels on the bf16 matrix cores: every float as three bf16 terms.
+
+The elementwise bound is the a-priori one of fp32 sums in any order, u = 2^-24
+per term; the dropped products (below 3 * 2^-26 of each) lie inside it.  Values
+for which the split is not exact, or whose products could overflow, take the
+fp32 matrix cores, so infinities, NaN and tiny values behave as in fp32.
+"""
+import numpy as np
+import pytest
+
+from oracle import oracle as orc
+from paper_2606_09905_amd import qx
+
+pytestmark = pytest.mark.gpu
+
+torch = pytest.importorskip("torch")
+U = 2.0 ** -24
+
+
+@pytest.fixture(scope="module", autouse=True)
+def _gpu():
+    if not torch.cuda.is_available():
+        pytest.fail("no GPU visible")
+    assert qx.lib() is not None
+
+
+def dev(a):
+    return torch.from_numpy(np.ascontiguousarray(a)).cuda()
+
+
+def host(t):
+    torch.cuda.synchronize()
+    return t.cpu().numpy()
+
+
+def core_bound(Q, K, V):
+    d, L = Q.shape[1], Q.shape[0]
+    return (d + L + 4) * U * ((np.abs(Q).astype(np.float64) @ np.abs(K).astype(np.float64).T) @ np.abs(V))
+
+
+# both workgroup sizes (128 and 256 queries), one and several key splits, one
+# key block, a last block of one key and of 31
+@pytest.mark.parametrize("L,d", [(1, 64), (33, 32), (63, 128), (129, 96), (160, 64), (4095, 64), (4128, 64),
+                                 (8193, 32), (2817, 96), (2080, 128)])
+def test_core(L, d):
+    rng = np.random.default_rng(L + d)
+    Q, K, V = ((rng.standard_normal((L, d)) * d ** -0.5).astype(np.float32) for _ in range(3))
+    O = host(qx.attn_core(dev(Q), dev(K), dev(V)))
+    assert (np.abs(O - orc.attn_f64(Q, K, V)) <= core_bound(Q, K, V)).all()
+
+
+@pytest.mark.parametrize("L", [96, 4352])
+@pytest.mark.parametrize("scales", [(2.0 ** 40, 2.0 ** -40, 1.0), (1.0, 1.0, 1e-36), (2.0 ** -70, 2.0 ** 60, 1e10)])
+def test_core_ranges(L, scales):
+    rng = np.random.default_rng(L)
+    Q, K, V = ((rng.standard_normal((L, 64)) * s).astype(np.float32) for s in scales)
+    O = host(qx.attn_core(dev(Q), dev(K), dev(V)))
+    # results below the smallest normal number lose up to its half ulp per term
+    assert (np.abs(O - orc.attn_f64(Q, K, V)) <= core_bound(Q, K, V) + L * 2.0 ** -149).all()
+
+
+@pytest.mark.parametrize("L", [70, 4352])
+@pytest.mark.parametrize("value", [np.inf, -np.inf, np.nan])
+def test_core_not_finite(L, value):
+    rng = np.random.default_rng(L)
+    Q, K, V = ((rng.standard_normal((L, 64)) * 0.125).astype(np.float32) for _ in range(3))
+    V[L - 2, 5] = value
+    Q[7, 3] = value
+    O = host(qx.attn_core(dev(Q), dev(K), dev(V)))
+    with np.errstate(invalid="ignore"):
+        R = (Q.astype(np.float64) @ K.astype(np.float64).T) @ V.astype(np.float64)
+    ok = np.ones_like(O, dtype=bool)
+    ok[7], ok[:, 5] = False, False          # row 7 sums infinities of both signs: NaN
+    assert np.isnan(O[7]).all()
+    rows = np.arange(L) != 7
+    assert np.array_equal(np.isnan(O[rows, 5]), np.isnan(R[rows, 5]))
+    if not np.isnan(value):
+        assert np.array_equal(O[rows, 5], R[rows, 5])
+    Q[7, 3], V[L - 2, 5] = 0.0, 0.0
+    bound = core_bound(Q, K, V)
+    assert (np.abs(O[ok] - R[ok]) <= bound[ok]).all()
+
+
+def sdpa_ref(Q, K, V, scale, causal):
+    return orc.sdpa_f64(Q, K, V, scale, causal)
+
+
+# the merged maximum of a row whose first key splits are masked, one wave and
+# eight, blocks past a wave's last query, ragged d on both workgroup sizes
+@pytest.mark.parametrize("BH,L,d,causal", [(1, 32, 64, True), (3, 97, 33, True), (1, 1025, 64, True),
+                                           (40, 257, 64, True), (9, 512, 80, True), (5, 1290, 31, False),
+                                           (4, 1281, 128, True), (2, 1100, 96, False)])
+def test_softmax(BH, L, d, causal):
+    rng = np.random.default_rng(BH + L + d)
+    Q, K, V = (rng.standard_normal((BH, L, d)).astype(np.float32) for _ in range(3))
+    O = host(qx.sdpa_f32(dev(Q), dev(K), dev(V), d ** -0.5, causal))
+    R = sdpa_ref(Q, K, V, d ** -0.5, causal)
+    # a score's error, (d + 4) u |q||k| scale, is the relative error of its exponential
+    s = (d + 4) * U * d ** -0.5 * np.abs(Q).max() * np.abs(K).max() * d + 8 * U
+    assert np.abs(O - R).max() <= (2 * s + L * U) * np.abs(V).max()
+    assert np.linalg.norm(O - R) <= 4e-6 * np.linalg.norm(R)
+
+
+@pytest.mark.parametrize("BH,L", [(2, 100), (20, 512)])
+def test_softmax_ranges(BH, L):
+    d = 64
+    rng = np.random.default_rng(L)
+    Q, K, V = (rng.standard_normal((BH, L, d)).astype(np.float32) for _ in range(3))
+    V0 = V.copy()
+    V[0] *= 1e-37                       # below the split's exact range
+    V[1] *= 1e30                        # and above it
+    K[1, 3, 5] = 1e-33
+    K[0, L - 1, 0] = np.inf             # an infinite score of either sign
+    O = host(qx.sdpa_f32(dev(Q), dev(K), dev(V), 0.125, True))
+    K[1, 3, 5] = 0.0
+    last = Q[0, L - 1, 0]
+    K[0, L - 1, 0] = 0.0
+    R = sdpa_ref(Q, K, V0, 0.125, True)
+    assert np.linalg.norm(O[0, :L - 1] / np.float64(1e-37) - R[0, :L - 1]) <= 2e-5 * np.linalg.norm(R[0, :L - 1])
+    assert np.linalg.norm(O[1] / np.float64(1e30) - R[1]) <= 4e-6 * np.linalg.norm(R[1])
+    if BH > 2:
+        assert np.linalg.norm(O[2:] - R[2:]) <= 4e-6 * np.linalg.norm(R[2:])
+    if last > 0:
+        assert np.isnan(O[0, L - 1]).all()      # exp(inf - inf)
