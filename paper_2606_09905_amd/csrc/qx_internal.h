@@ -123,8 +123,6 @@ struct Im2colTParams {
 // Implicit lowering of a convolution (C_in a multiple of 64): the input as a
 // zero-bordered NHWC fp16 copy xp [N][H+2pad][W+2pad][Ci] and the weights as
 // w16 [Cop][Kd] fp16 with k = (kh*KW + kw)*Ci + ci, in one launch.
-// elem_bytes 2: int16 in, fp16 out (C_in a multiple of 64); 4: float32
-// copied unchanged (C_in a multiple of 32).
 struct ConvPrepParams {
     const void* x;          // NCHW
     const void* w;          // OIHW
@@ -132,7 +130,23 @@ struct ConvPrepParams {
     void* w16;
     int32_t nimg, Co, Cop, Kd;
     int32_t xblocks, wblocks;
-    int32_t elem_bytes;
+    ConvGeom g;
+};
+
+// FP32 convolution on split operands (C_in a multiple of 32): the prep and
+// contraction launches share one block.
+struct ConvF32Params {
+    const float* x;         // NCHW
+    const float* w;         // OIHW
+    float* y;               // NCHW
+    unsigned char* xs;      // [N][H+2pad][W+2pad][Ci/32][3][32] bf16
+    unsigned char* ws;      // [Cop][Kd/32][3][32] bf16, k = (kh*KW + kw)*Ci + ci
+    int32_t nimg, Co, Cop, Kd;
+    int32_t P, hw;          // N*Ho*Wo, Ho*Wo
+    int32_t xblocks;        // prep: leading blocks that make the image
+    int32_t tiles_per_split; // K tiles per split (grid y)
+    float* part;            // several splits: partial outputs [splits][part_stride], as y
+    int64_t part_stride;
     ConvGeom g;
 };
 
@@ -223,9 +237,9 @@ struct SdpaCombineParams {
 };
 
 struct ReduceParams {
-    const float* part;      // [splits][n]
+    const float* part;      // [splits][stride], stride a multiple of 4
     float* out;             // [n]
-    int64_t n;
+    int64_t n, stride;
     int32_t splits;
 };
 
@@ -397,8 +411,10 @@ void build_enc_a(const EncParams& p, LaunchRec* rec);
 void build_enc_bt(const EncParams& p, LaunchRec* rec);
 void build_im2col_t(const Im2colTParams& p, LaunchRec* rec);
 void build_conv_prep(const ConvPrepParams& p, LaunchRec* rec);
-// FP32 NT GEMM on the fp32 matrix cores (conv FP32 row); same tile shapes.
-void build_gemm_nt_f32(const GemmParams& p, int batch, LaunchRec* rec);
+// FP32 convolution: the contraction's tile (64 channels x bn pixels) and K
+// splits of `per` 32-k tiles, and the prep and contraction launches.
+void conv_f32_shape(int64_t Co, int64_t P, int64_t Kd, int* bn, int64_t* splits, int64_t* per);
+void build_conv_f32(const ConvF32Params& p, int bn, int splits, LaunchRec* prep, LaunchRec* rec);
 // int8 limb routes for large problems: limb-plane encoders + direct-to-LDS NT GEMM.
 void i8nt_tile_shape(int32_t route, int64_t M, int64_t N, int64_t batch, int* bm, int* bn);
 void build_enc_limb(int32_t route, bool s24, const EncPairParams& p, LaunchRec* rec);

@@ -122,3 +122,45 @@ def test_softmax_ranges(BH, L):
         assert np.linalg.norm(O[2:] - R[2:]) <= 4e-6 * np.linalg.norm(R[2:])
     if last > 0:
         assert np.isnan(O[0, L - 1]).all()      # exp(inf - inf)
+
+
+# N, C_in, H, W, C_out, K, stride, pad: one tile and many, C_out and pixels off
+# the tiles' edges, K splits with a short last one and outputs not a multiple
+# of 4, stride 2, tap ranges that start inside a tap's channels
+CONV = [(1, 32, 1, 1, 1, 1, 1, 0), (1, 64, 7, 9, 33, 3, 1, 1), (3, 96, 5, 7, 65, 3, 2, 1), (1, 256, 7, 7, 130, 3, 1, 1),
+        (2, 160, 13, 11, 63, 5, 1, 2), (7, 32, 56, 57, 128, 3, 1, 1), (1, 224, 3, 3, 5, 3, 1, 0)]
+
+
+def conv_ref(x, w, stride, pad):
+    t = [torch.from_numpy(a.astype(np.float64)) for a in (x, w)]
+    return torch.nn.functional.conv2d(*t, stride=stride, padding=pad).numpy()
+
+
+@pytest.mark.parametrize("case", CONV)
+def test_conv(case):
+    N, Ci, H, W, Co, k, stride, pad = case
+    rng = np.random.default_rng(sum(case))
+    x = rng.standard_normal((N, Ci, H, W)).astype(np.float32)
+    w = rng.standard_normal((Co, Ci, k, k)).astype(np.float32)
+    y = host(qx.conv2d_gemm_t(dev(x), dev(w), stride, pad))
+    bound = (Ci * k * k + 4) * U * conv_ref(np.abs(x), np.abs(w), stride, pad)
+    assert (np.abs(y - conv_ref(x, w, stride, pad)) <= bound).all()
+    assert np.array_equal(y, host(qx.conv2d_gemm_t(dev(x), dev(w), stride, pad)))
+
+
+@pytest.mark.parametrize("case", [CONV[2], CONV[3], CONV[5]])
+@pytest.mark.parametrize("value", [np.inf, np.nan, 3e-38, 1e25])
+def test_conv_out_of_range(case, value):
+    N, Ci, H, W, Co, k, stride, pad = case
+    rng = np.random.default_rng(sum(case))
+    x = rng.standard_normal((N, Ci, H, W)).astype(np.float32)
+    w = rng.standard_normal((Co, Ci, k, k)).astype(np.float32)
+    x[N - 1, 3, 2, 1] = value
+    w[Co // 2, Ci - 1, k - 1, 0] = value
+    y = host(qx.conv2d_gemm_t(dev(x), dev(w), stride, pad))
+    with np.errstate(invalid="ignore"):
+        R, A = conv_ref(x, w, stride, pad), conv_ref(np.abs(x), np.abs(w), stride, pad)
+    fin = np.isfinite(R)
+    assert np.array_equal(np.isfinite(y), fin)
+    assert np.array_equal(np.isnan(y), np.isnan(R))
+    assert (np.abs(y[fin].astype(np.float64) - R[fin]) <= (Ci * k * k + 4) * U * A[fin]).all()
