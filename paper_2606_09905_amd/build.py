@@ -34,8 +34,10 @@ FLAGS = [
 # Per-source additions.  The attention kernels keep their MFMA accumulators
 # in ordinary VGPRs: the online softmax rescales the output accumulators
 # with vector ALU multiplies, and accumulators placed in AGPRs would be
-# copied out and back around every key block.
-EXTRA = {"k_attn.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form"]}
+# copied out and back around every key block.  Likewise the pooled
+# convolutions of k_reduce.hip, which shift their accumulators between limbs.
+EXTRA = {"k_attn.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form"],
+         "k_reduce.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form"]}
 
 
 def _compile(src: str) -> str:

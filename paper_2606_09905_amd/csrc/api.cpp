@@ -1106,38 +1106,16 @@ qx_status plan_lenet(Plan* pl, int64_t B) {
         append_plan(pl, sp, take((uint64_t)sp.info.workspace_bytes), ins, out);
         return QX_OK;
     };
-    auto pool = [&](uint64_t from, uint64_t to, int64_t C, int32_t H) {
-        PoolParams pp{};
-        pp.NC = B * C; pp.H = H; pp.W = H; pp.Ho = H / 2; pp.Wo = H / 2;
-        pp.vec = H % 8 == 0 ? 1 : 0;
-        pp.relu = 1;
+    // conv 5x5 (smul24), ReLU and the 2x2 average pool into the workspace, one launch
+    auto conv_pool = [&](int layer, Target x, Bind w, uint64_t to) {
+        ConvPoolParams cp{};
+        cp.nimg = (int32_t)B;
         LaunchRec r;
-        build_pool2(POOL_AVG_I32, pp, &r);
-        r.bind(offsetof(PoolParams, x), BIND_WS, from);
-        r.bind(offsetof(PoolParams, y), BIND_WS, to);
+        build_conv_pool(layer, cp, &r);
+        r.bind(offsetof(ConvPoolParams, x), x.bind, x.add);
+        r.bind(offsetof(ConvPoolParams, w), w);
+        r.bind(offsetof(ConvPoolParams, y), BIND_WS, to);
         pl->launches.push_back(r);
-    };
-    // conv 5x5 (smul24, few output channels: the direct kernel), ReLU and the
-    // 2x2 average pool into the workspace: one launch (one thread per pooled
-    // pixel) when an image fits the kernel's LDS, else the conv and the pool
-    // as two launches.  The second conv at batch 4096 fused: 48.8 us against
-    // 49.6 + 11.5 (the grid is smaller, 1.6 waves per SIMD, but its busiest
-    // CUs carry the same work and the conv map never reaches HBM).
-    auto conv_pool = [&](Target x, Bind w, uint64_t to, int64_t Ci, int32_t H, int64_t Co) {
-        const int32_t Ho = H - 4;
-        ConvDirectParams cd{};
-        cd.P = B * Ho * Ho; cd.Co = (int32_t)Co; cd.Kd = (int32_t)(Ci * 25);
-        cd.g = ConvGeom{(int32_t)Ci, H, H, 5, 5, 1, 0, Ho, Ho};
-        const bool fuse = conv_pool_images(cd) > 0;
-        cd.pool = fuse ? 1 : 0;
-        const uint64_t y = fuse ? to : take(4 * (uint64_t)B * Co * Ho * Ho);
-        LaunchRec r;
-        build_conv_direct_s24(cd, &r);
-        r.bind(offsetof(ConvDirectParams, x), x.bind, x.add);
-        r.bind(offsetof(ConvDirectParams, w), w);
-        r.bind(offsetof(ConvDirectParams, y), BIND_WS, y);
-        pl->launches.push_back(r);
-        if (!fuse) pool(y, to, Co, Ho);
     };
     // ReLU after a fully connected layer: folded into the stores of the
     // layer's last launch when that is the int8 NT contraction (K not
@@ -1168,8 +1146,8 @@ qx_status plan_lenet(Plan* pl, int64_t B) {
         pl->launches.push_back(r);
     };
     Plan g1, g2, g3;
-    conv_pool({BIND_IN0, 0}, BIND_IN1, o_p1, 1, 32, 6);
-    conv_pool({BIND_WS, o_p1}, BIND_IN2, o_p2, 6, 14, 16);
+    conv_pool(1, {BIND_IN0, 0}, BIND_IN1, o_p1);
+    conv_pool(2, {BIND_WS, o_p1}, BIND_IN2, o_p2);
     if ((st = plan_gemm(&g1, true, B, 120, 400, 1, 0, 0, R_AUTO))) return st;
     if ((st = sub(g1, {{BIND_WS, o_p2}, {BIND_IN3, 0}}, {BIND_WS, o_h1}))) return st;
     relu(o_h1, B * 120);

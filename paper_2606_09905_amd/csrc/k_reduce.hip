@@ -4,6 +4,7 @@
 // 16-byte loads; their roofline is HBM bandwidth.
 #include <algorithm>
 
+#include "conv_pool.h"
 #include "qx_internal.h"
 
 namespace qx {
@@ -374,106 +375,6 @@ void k_conv_direct_s24(const ConvDirectParams p) {
                 for (int j = 0; j < PXT; ++j) p.y[((int64_t)n * p.Co + c) * hw + rem + j] = (int32_t)acc[j][c];
 }
 
-// The direct convolution fused with ReLU and a 2x2 average pool (the
-// sequence of the LeNet-shaped pipeline): a thread computes one 2x2 block of
-// conv outputs for every output channel (four pixels share each weight
-// read, as above) and writes only the pooled value, floor((relu(a) +
-// relu(b) + relu(c) + relu(d)) / 4) summed in 64 bits, the pool kernel's
-// arithmetic.  Ho and Wo even; the output is [N][C_out][Ho/2][Wo/2].  A
-// workgroup takes p.imgs whole images, staged in LDS as above.
-template <int DCO, int KWT, bool S1P0, int DCU>
-__global__ __launch_bounds__(RT) void k_conv_pool_s24(const ConvDirectParams p) {
-    extern __shared__ __align__(16) int32_t wsh[];
-    int32_t(*ws)[DCO] = (int32_t(*)[DCO])wsh;
-    const ConvGeom& g = p.g;
-    stage_weights<DCO>(ws, p.w, p.Co, p.Kd);
-    const int Wq = g.Wo / 2, hwq = (g.Ho / 2) * Wq;
-    const int64_t pq = p.P / 4;   // pooled pixels
-    // images [img0, img0 + cnt) of the batch; thread -> one pooled pixel
-    const int imgs = p.imgs, nimg = (int)(pq / hwq);
-    const int img0 = (int)blockIdx.x * imgs, cnt = min(imgs, nimg - img0);
-    const int chw = g.Ci * g.H * g.W;
-    int32_t* xs = wsh + p.Kd * DCO;
-    copy_to_lds(xs, p.x + (int64_t)img0 * chw, cnt * chw);
-    const int local = (int)threadIdx.x;
-    const bool live = local < cnt * hwq;
-    const int li = min(local, cnt * hwq - 1);
-    const int limg = li / hwq;
-    const int remq = li - limg * hwq;
-    const int n = img0 + limg;
-    const int32_t* xb = xs + (int64_t)limg * chw;
-    __syncthreads();
-    const int qh = remq / Wq, qw = remq - qh * Wq;
-    const int oh0 = 2 * qh, ow0 = 2 * qw;
-    // DCU: output channels computed (C_out <= DCU <= DCO; the LDS weight
-    // rows stay DCO wide)
-    static_assert(DCU <= DCO, "computed channels fit the weight rows");
-    uint32_t acc[4][DCU];
-#pragma unroll
-    for (int j = 0; j < 4; ++j)
-#pragma unroll
-        for (int c = 0; c < DCU; ++c) acc[j][c] = 0u;
-    int k = 0;
-    for (int ci = 0; ci < g.Ci; ++ci)
-        for (int kh = 0; kh < g.KH; ++kh, k += g.KW) {
-            int32_t xv[4][KWT];
-#pragma unroll
-            for (int dy = 0; dy < 2; ++dy) {
-                if constexpr (S1P0) {
-                    // stride 1, no padding: the two pixels of a row share
-                    // KW - 1 of their inputs, all inside the image
-                    const int32_t* xr = xb + ((int64_t)ci * g.H + oh0 + dy + kh) * g.W + ow0;
-                    int32_t xrow[KWT + 1];
-#pragma unroll
-                    for (int i = 0; i < KWT + 1; ++i) xrow[i] = (KWT != DKW || i < g.KW + 1) ? xr[i] : 0;
-#pragma unroll
-                    for (int dx = 0; dx < 2; ++dx)
-#pragma unroll
-                        for (int kw = 0; kw < KWT; ++kw)
-                            xv[2 * dy + dx][kw] = (KWT != DKW || kw < g.KW) ? xrow[dx + kw] : 0;
-                } else {
-                    const int ih = (oh0 + dy) * g.stride - g.pad + kh;
-                    const bool rin = ih >= 0 && ih < g.H;
-                    const int32_t* xr = xb + ((int64_t)ci * g.H + ih) * g.W;
-#pragma unroll
-                    for (int dx = 0; dx < 2; ++dx)
-#pragma unroll
-                        for (int kw = 0; kw < KWT; ++kw) {
-                            const int iw = (ow0 + dx) * g.stride - g.pad + kw;
-                            xv[2 * dy + dx][kw] = (kw < g.KW && rin && iw >= 0 && iw < g.W) ? xr[iw] : 0;
-                        }
-                }
-            }
-            // the kernel row's weights first, all reads in flight together
-            int32_t wr[KWT][DCO];
-#pragma unroll
-            for (int kw = 0; kw < KWT; ++kw) {
-                const i4v* wk = (const i4v*)ws[k + (KWT == DKW ? min(kw, g.KW - 1) : kw)];
-#pragma unroll
-                for (int c4 = 0; c4 < (DCU + 3) / 4; ++c4) {
-                    const i4v w4 = wk[c4];
-#pragma unroll
-                    for (int e = 0; e < 4; ++e) wr[kw][4 * c4 + e] = w4[e];
-                }
-            }
-#pragma unroll
-            for (int kw = 0; kw < KWT; ++kw)
-#pragma unroll
-                for (int j = 0; j < 4; ++j)
-#pragma unroll
-                    for (int c = 0; c < DCU; ++c) acc[j][c] += (uint32_t)__mul24(xv[j][kw], wr[kw][c]);
-        }
-    if (live)
-#pragma unroll
-        for (int c = 0; c < DCU; ++c)
-            if (c < p.Co) {
-                int64_t sum = 0;
-#pragma unroll
-                for (int j = 0; j < 4; ++j) sum += max((int64_t)(int32_t)acc[j][c], (int64_t)0);
-                p.y[((int64_t)n * p.Co + c) * hwq + remq] = (int32_t)(sum >> 2);
-            }
-}
-
 // ---------------------------------------------------------------------------
 // Builders
 // ---------------------------------------------------------------------------
@@ -498,46 +399,25 @@ void build_minmax(const MinMaxParams& p, LaunchRec* partial, LaunchRec* final_re
     final_rec->set_params(p);
 }
 
-// Whole images per workgroup for the fused conv + ReLU + pool kernel: as
-// many as its threads (one per pooled pixel) and 64 KB of LDS (weights and
-// inputs) hold; 0 when not even one fits.
-int32_t conv_pool_images(const ConvDirectParams& p) {
-    const int dco = p.Co <= 8 ? 8 : 16;
-    const int64_t hwq = (int64_t)(p.g.Ho / 2) * (p.g.Wo / 2);
-    const int64_t chw = (int64_t)p.g.Ci * p.g.H * p.g.W;
-    if (hwq <= 0 || chw <= 0 || p.P <= 0) return 0;
-    return (int32_t)std::max<int64_t>(std::min<int64_t>(RT / hwq, (16384 - (int64_t)p.Kd * dco) / chw), 0);
+// Images per workgroup: four (196 positions each, tiles of 32) and eight (25
+// positions each, tiles of 16), fewer while the batch leaves CUs idle.  Batch
+// 4096, conv1 22.0 us with four (23.3 with two, 23.4 with eight) and conv2
+// 19.4 with eight (22.7 with five, 23.9 with sixteen); one pooled pixel per
+// thread on the vector ALU (v_mad_i32_i24) took 29.3 and 48.7 us.
+void build_conv_pool(int layer, const ConvPoolParams& p0, LaunchRec* rec) {
+    ConvPoolParams p = p0;
+    const int full = layer == 1 ? 4 : 8;
+    p.imgs = std::min(full, std::max(1, p.nimg / 256));
+    rec->fn = layer == 1 ? (const void*)k_conv1_pool : (const void*)k_conv2_pool;
+    rec->grid = dim3((unsigned)((p.nimg + p.imgs - 1) / p.imgs), 1, 1);
+    rec->block = dim3(CP_THREADS, 1, 1);
+    rec->shmem = (uint32_t)(3 * (p.imgs * (layer == 1 ? 1024 : 1568) + 16));
+    rec->name = layer == 1 ? "conv1_relu_pool_s24" : "conv2_relu_pool_s24";
+    rec->set_params(p);
 }
 
 void build_conv_direct_s24(const ConvDirectParams& p0, LaunchRec* rec) {
     ConvDirectParams p = p0;
-    if (p.pool) {
-        // fused ReLU + 2x2 average: one thread per pooled pixel, whole
-        // images staged in LDS (the caller checked conv_pool_images > 0)
-        const int kw = p.g.KW;
-        const int dco = p.Co <= 8 ? 8 : 16;
-        const int64_t hwq = (int64_t)(p.g.Ho / 2) * (p.g.Wo / 2);
-        const int64_t chw = (int64_t)p.g.Ci * p.g.H * p.g.W;
-        p.imgs = conv_pool_images(p);
-        const bool s1p0 = p.g.stride == 1 && p.g.pad == 0;
-        // channels computed: C_out rounded up to 4, 6, 8 or 16
-#define QX_CP3(DCO, KWT, DCU) (s1p0 ? (const void*)k_conv_pool_s24<DCO, KWT, true, DCU> \
-                                    : (const void*)k_conv_pool_s24<DCO, KWT, false, DCU>)
-#define QX_CP2(DCO, KWT) (DCO == 16 ? QX_CP3(DCO, KWT, DCO) : p.Co <= 4 ? QX_CP3(DCO, KWT, 4) \
-                          : p.Co <= 6 ? QX_CP3(DCO, KWT, 6) : QX_CP3(DCO, KWT, DCO))
-#define QX_CP(DCO) (kw == 5 ? QX_CP2(DCO, 5) : kw == 3 ? QX_CP2(DCO, 3) : QX_CP2(DCO, DKW))
-        rec->fn = p.Co <= 8 ? QX_CP(8) : QX_CP(16);
-#undef QX_CP
-#undef QX_CP2
-#undef QX_CP3
-        const int64_t blocks = (p.P / 4 / hwq + p.imgs - 1) / p.imgs;
-        rec->grid = dim3((unsigned)std::max<int64_t>(blocks, 1), 1, 1);
-        rec->block = dim3(RT, 1, 1);
-        rec->shmem = (uint32_t)((p.Kd * dco + p.imgs * chw) * sizeof(int32_t));
-        rec->name = "conv_relu_pool_s24";
-        rec->set_params(p);
-        return;
-    }
     const int kw = p.g.KW, wo = p.g.Wo;
     const int pxt = wo % 4 == 0 ? 4 : wo % 2 == 0 ? 2 : 1;
     const int dco = p.Co <= 8 ? 8 : 16;
