@@ -144,11 +144,24 @@ def _torch():
     return torch
 
 
+_current = None   # (device getter, current raw stream of a device), once CUDA is initialised
+
+
 def _stream(stream):
     """The HIP stream handle (an int) of a torch stream, a raw handle, or
     None for torch's current stream."""
+    global _current
     if stream is None:
-        return _torch().cuda.current_stream().cuda_stream
+        # the handle straight from torch's native getters where it has them:
+        # building a Stream object costs as much as the rest of a small call
+        if _current is not None:
+            return _current[1](_current[0]())
+        torch = _torch()
+        handle = torch.cuda.current_stream().cuda_stream
+        get = [getattr(torch._C, n, None) for n in ("_cuda_getDevice", "_cuda_getCurrentRawStream")]
+        if all(get):
+            _current = tuple(get)
+        return handle
     handle = getattr(stream, "cuda_stream", None)
     return handle if handle is not None else int(stream)
 
@@ -403,6 +416,8 @@ class Executor:
         self.out_shape = tuple(out_shape)
         self.out_dtype = out_dtype
         self.n_inputs = n_inputs
+        self._ptrs = ctypes.c_void_p * n_inputs
+        self._run = lib().qx_exec_run
 
     @classmethod
     def gemm_i16i32(cls, M, N, K, batch=1, bound_a=0, bound_b=0, route="auto"):
@@ -500,20 +515,20 @@ class Executor:
     def run_ptrs(self, in_ptrs, out_ptr: int, stream=None) -> None:
         """Enqueue with raw device pointers (ints).  Kept lean: for small
         problems the host's cost per call is what bounds back-to-back runs."""
-        arr = (ctypes.c_void_p * len(in_ptrs))(*in_ptrs)
-        st = lib().qx_exec_run(self._h, arr, out_ptr, _stream(stream))
+        n = len(in_ptrs)
+        arr = self._ptrs(*in_ptrs) if n == self.n_inputs else (ctypes.c_void_p * n)(*in_ptrs)
+        st = self._run(self._h, arr, out_ptr, _stream(stream))
         if st != OK:
             check(st)
 
     def run(self, inputs, out=None, stream=None):
-        torch = _torch()
         if len(inputs) != self.n_inputs:
             raise ValueError(f"expected {self.n_inputs} inputs")
         if out is None:
-            out = torch.empty(self.out_shape, dtype=self.out_dtype, device=inputs[0].device)
+            out = _torch().empty(self.out_shape, dtype=self.out_dtype, device=inputs[0].device)
         ptrs = []
         for i, t in enumerate(inputs):
-            if t.device.type != "cuda" or not t.is_contiguous():
+            if not t.is_cuda or not t.is_contiguous():
                 raise ValueError(f"input {i} must be a contiguous GPU tensor")
             ptrs.append(t.data_ptr())
         if not out.is_contiguous() or out.dtype != self.out_dtype:
