@@ -543,6 +543,12 @@ qx_status plan_int_gemm(const GemmSpec& s, Plan* pl, uint64_t* ws_used) {
         g.chunk_tiles = chunk >= 64 ? (int32_t)(chunk / 64) : 0;
         info.chunk = chunk >= 64 ? (int32_t)(chunk / 64 * 64) : 16;
     }
+    // K slices add into the output, cleared first, so it must be one dense block
+    const bool dense_out = s.out_mode == OUT_CONV ||
+                           (s.ldc == s.N && (s.batch == 1 || s.sC == s.M * s.N));
+    g.ksplit = dense_out ? reg_staged_ksplit(route, s.M, s.N, s.K, s.batch) : 1;
+    info.k_splits = g.ksplit > 1 ? g.ksplit : 0;
+    if (g.ksplit > 1) add_fill_out(pl, s.M * s.N * s.batch);
     LaunchRec rec;
     int tm = 0, tn = 0, tk = 0;
     if (!build_gemm_mfma(route, g, (int)s.batch, &rec, &tm, &tn, &tk))

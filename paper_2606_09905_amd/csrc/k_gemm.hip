@@ -35,6 +35,7 @@ typedef unsigned u16x __attribute__((ext_vector_type(16)));
 typedef int i4 __attribute__((ext_vector_type(4)));
 typedef short s8 __attribute__((ext_vector_type(8)));
 typedef short s4 __attribute__((ext_vector_type(4)));
+typedef uint32_t u2 __attribute__((ext_vector_type(2)));
 
 constexpr int NT = 256;  // threads per workgroup (4 waves)
 
@@ -64,6 +65,54 @@ __device__ __forceinline__ void store_c(const GemmParams& p, int32_t* C, int gm,
     C[c_index(p, gm, gn)] = (int32_t)v;
 }
 
+// Column gn of C: its first element, with the distance between rows.
+__device__ __forceinline__ int32_t* c_column(const GemmParams& p, int32_t* C, int gn, int64_t& stride) {
+    if (p.out_mode == OUT_ROWMAJOR) {
+        stride = p.ldc;
+        return C + gn;
+    }
+    const int img = gn / p.hw, pix = gn - img * p.hw;
+    stride = p.hw;
+    return C + (int64_t)img * p.M * p.hw + pix;
+}
+
+// Store, or (ADD: K sliced over grid y) wrapping add into a cleared C, exact
+// in any order.
+template <bool ADD>
+__device__ __forceinline__ void put_c(int32_t* c, uint32_t v) {
+    if (ADD) atomicAdd((uint32_t*)c, v);
+    else *c = (int32_t)v;
+}
+
+// This workgroup's K tiles [t0, t1) of 64 (grid y slices K).
+__device__ __forceinline__ void k_slice(const GemmParams& p, int& t0, int& t1) {
+    const int ktiles = (p.K + 63) / 64;
+    if (p.ksplit > 1) {
+        const int per = (ktiles + p.ksplit - 1) / p.ksplit;
+        t0 = (int)blockIdx.y * per;
+        t1 = min(t0 + per, ktiles);
+    } else {
+        t0 = 0;
+        t1 = ktiles;
+    }
+}
+
+// N consecutive elements of a row from column c, the row ending at column
+// `end`: one vector load at the element's alignment where they lie inside,
+// else one load each, the last element in place of those past the end.
+template <class T, int N>
+__device__ __forceinline__ void load_row(const T* row, int c, int end, T (&dst)[N]) {
+    typedef T V __attribute__((ext_vector_type(N), aligned(sizeof(T))));
+    if (c + N <= end) {
+        const V x = *(const V*)(row + c);
+#pragma unroll
+        for (int e = 0; e < N; ++e) dst[e] = x[e];
+    } else {
+#pragma unroll
+        for (int e = 0; e < N; ++e) dst[e] = row[min(c + e, end - 1)];
+    }
+}
+
 // ===========================================================================
 // F16_EXACT
 // ===========================================================================
@@ -73,7 +122,7 @@ __device__ __forceinline__ void store_c(const GemmParams& p, int32_t* C, int gm,
 __device__ __forceinline__ int swz_a(int row, int c) { return c ^ (row & 7); }
 __device__ __forceinline__ int swz_b(int col, int c) { return c ^ ((col ^ (col >> 3)) & 7); }
 
-template <int BM, int BN, int BK, int WM, int WN, bool ALIGNED, bool FLUSH_STEP>
+template <int BM, int BN, int BK, int WM, int WN, bool FLUSH_STEP>
 __global__ __launch_bounds__(NT) void k_gemm_f16x(const GemmParams p) {
     static_assert(BK == 64, "chunk swizzle assumes 8 chunks per row");
     constexpr int KCH = BK / 8;
@@ -99,35 +148,27 @@ __global__ __launch_bounds__(NT) void k_gemm_f16x(const GemmParams p) {
     const int16_t* B = (const int16_t*)p.B + b * p.sB;
     int32_t* C = (int32_t*)p.C + b * p.sC;
 
-    s8 ra[A_VECS];
-    s8 rb[4];
+    int16_t ra[A_VECS][8];
+    int16_t rb[4][8];
     const int bkb = tid / B_NBLK, bnb = tid % B_NBLK;
 
+    // Rows and columns past the operands repeat the last ones (their outputs
+    // are not stored); k past K is 0 in A, so B's there may be anything.
     auto load = [&](int k0) {
 #pragma unroll
         for (int i = 0; i < A_VECS; ++i) {
-            const int v = tid + NT * i, row = v / KCH, c = v % KCH;
-            const int gm = m0 + row, gk = k0 + c * 8;
-            if (ALIGNED) {
-                ra[i] = (gm < p.M && gk < p.K) ? *(const s8*)(A + (int64_t)gm * p.lda + gk) : s8{};
-            } else {
+            const int v = tid + NT * i, row = v / KCH, gk = k0 + v % KCH * 8;
+            load_row(A + (int64_t)min(m0 + row, p.M - 1) * p.lda, gk, p.K, ra[i]);
+            if (k0 + BK > p.K) {
 #pragma unroll
                 for (int e = 0; e < 8; ++e)
-                    ra[i][e] = (gm < p.M && gk + e < p.K) ? A[(int64_t)gm * p.lda + gk + e] : (short)0;
+                    if (gk + e >= p.K) ra[i][e] = 0;
             }
         }
         if (B_THREADS < NT && tid >= B_THREADS) return;
 #pragma unroll
-        for (int r = 0; r < 4; ++r) {
-            const int gk = k0 + bkb * 4 + r, gn = n0 + bnb * 8;
-            if (ALIGNED) {
-                rb[r] = (gk < p.K && gn < p.N) ? *(const s8*)(B + (int64_t)gk * p.ldb + gn) : s8{};
-            } else {
-#pragma unroll
-                for (int e = 0; e < 8; ++e)
-                    rb[r][e] = (gk < p.K && gn + e < p.N) ? B[(int64_t)gk * p.ldb + gn + e] : (short)0;
-            }
-        }
+        for (int r = 0; r < 4; ++r)
+            load_row(B + (int64_t)min(k0 + bkb * 4 + r, p.K - 1) * p.ldb, n0 + bnb * 8, p.N, rb[r]);
     };
     auto stash = [&](int buf) {
 #pragma unroll
@@ -170,7 +211,9 @@ __global__ __launch_bounds__(NT) void k_gemm_f16x(const GemmParams p) {
             }
     };
 
-    const int ktiles = (p.K + BK - 1) / BK;
+    int t0, t1;
+    k_slice(p, t0, t1);
+    if (t0 >= t1) return;
     // The MFMA steps of one staged K tile.  With FLUSH_STEP each step's
     // product block is a whole chunk (16 k): it starts from zero and is
     // converted and added on its own.
@@ -204,34 +247,42 @@ __global__ __launch_bounds__(NT) void k_gemm_f16x(const GemmParams p) {
         }
     };
     int since_flush = 0;
-    load(0);
-    stash(0);
+    load(t0 * BK);
+    stash(t0 & 1);
     __syncthreads();
-    for (int t = 0; t < ktiles; ++t) {
+    for (int t = t0; t < t1; ++t) {
         const int buf = t & 1;
-        if (t + 1 < ktiles) load((t + 1) * BK);
+        if (t + 1 < t1) load((t + 1) * BK);
         compute(buf);
         if (!FLUSH_STEP && ++since_flush == p.chunk_tiles) {
             flush();
             since_flush = 0;
         }
-        if (t + 1 < ktiles) stash(buf ^ 1);
+        if (t + 1 < t1) stash(buf ^ 1);
         __syncthreads();
     }
     if (!FLUSH_STEP) flush();
 
     // 32x32 accumulator layout: lane holds column (lane & 31) and rows
     // 8*(r/4) + 4*(lane/32) + r%4.
+    auto put = [&](auto add) {
 #pragma unroll
-    for (int i = 0; i < TM; ++i)
+        for (int j = 0; j < TN; ++j) {
+            const int gn = n0 + wn * WN + j * 32 + (lane & 31);
+            if (gn >= p.N) continue;
+            int64_t stride;
+            int32_t* c = c_column(p, C, gn, stride);
 #pragma unroll
-        for (int j = 0; j < TN; ++j)
+            for (int i = 0; i < TM; ++i)
 #pragma unroll
-            for (int r = 0; r < 16; ++r) {
-                const int gm = m0 + wm * WM + i * 32 + 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3);
-                const int gn = n0 + wn * WN + j * 32 + (lane & 31);
-                store_c(p, C, gm, gn, iacc[i][j][r]);
-            }
+                for (int r = 0; r < 16; ++r) {
+                    const int gm = m0 + wm * WM + i * 32 + 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3);
+                    if (gm < p.M) put_c<decltype(add)::value>(c + gm * stride, iacc[i][j][r]);
+                }
+        }
+    };
+    if (p.ksplit > 1) put(std::true_type{});
+    else put(std::false_type{});
 }
 
 // Small fp16-exact GEMMs (K <= 256): a workgroup owns a 32 x 32 output tile
@@ -408,179 +459,6 @@ __device__ __forceinline__ void load_vec(const T* src, T (&dst)[N]) {
     for (int e = 0; e < N; ++e) dst[e] = x.v[e];
 }
 
-// 64-byte LDS rows (BK = 64 int8) as four 16-byte chunks; the swizzle keeps
-// the eight rows of one ds_read_b128 pass in distinct banks.
-__device__ __forceinline__ int swz8(int row, int c) { return c ^ ((row >> 1) & 3); }
-
-template <class S, class T, int BM, int BN, int WM, int WN, bool ALIGNED>
-__global__ __launch_bounds__(NT) void k_gemm_i8limb(const GemmParams p) {
-    constexpr int BK = 64, KCH = 4;
-    constexpr int P = S::PLANES, G = S::GROUPS;
-    constexpr int TM = WM / 32, TN = WN / 32;
-    constexpr int WAVES_N = BN / WN;
-    static_assert((BM / WM) * (BN / WN) == 4, "four waves");
-    constexpr int A_VECS = BM * BK / 8 / NT;      // 8-element A vectors per thread
-    constexpr int BWN = BN / 16;                  // B staged as 4(k) x BWN(n) blocks
-    static_assert((BK / 4) * (BN / BWN) == NT, "one B block per thread");
-
-    __shared__ i4 As[2][P][BM][KCH];
-    __shared__ i4 Bs[2][P][BN][KCH];
-
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int wm = wave / WAVES_N, wn = wave % WAVES_N;
-    const int tiles_m = (p.M + BM - 1) / BM;
-    int tm, tn;
-    tile_coords(tiles_m, p.tiles_n, tm, tn);
-    const int m0 = tm * BM, n0 = tn * BN;
-    const int b = blockIdx.z;
-    const T* A = (const T*)p.A + b * p.sA;
-    const T* B = (const T*)p.B + b * p.sB;
-    int32_t* C = (int32_t*)p.C + b * p.sC;
-
-    T ra[A_VECS][8];
-    T rb[4][BWN];
-    const int bkb = tid / (BN / BWN), bnb = tid % (BN / BWN);
-
-    auto load = [&](int k0) {
-#pragma unroll
-        for (int i = 0; i < A_VECS; ++i) {
-            const int v = tid + NT * i, row = v / 8, e8 = v % 8;
-            const int gm = m0 + row, gk = k0 + e8 * 8;
-            const T* src = A + (int64_t)gm * p.lda + gk;
-            if (ALIGNED && gm < p.M && gk < p.K) {
-                load_vec<T, 8>(src, ra[i]);
-            } else {
-#pragma unroll
-                for (int e = 0; e < 8; ++e) ra[i][e] = (gm < p.M && gk + e < p.K) ? src[e] : (T)S::PAD;
-            }
-        }
-#pragma unroll
-        for (int r = 0; r < 4; ++r) {
-            const int gk = k0 + bkb * 4 + r, gn = n0 + bnb * BWN;
-            const T* src = B + (int64_t)gk * p.ldb + gn;
-            if (ALIGNED && gk < p.K && gn < p.N) {
-                load_vec<T, BWN>(src, rb[r]);
-            } else {
-#pragma unroll
-                for (int e = 0; e < BWN; ++e) rb[r][e] = (gk < p.K && gn + e < p.N) ? src[e] : (T)S::PAD;
-            }
-        }
-    };
-    auto stash = [&](int buf) {
-#pragma unroll
-        for (int i = 0; i < A_VECS; ++i) {
-            const int v = tid + NT * i, row = v / 8, e8 = v % 8;
-            uint32_t w[P][2] = {};
-#pragma unroll
-            for (int e = 0; e < 8; ++e) {
-                uint32_t l[P];
-                S::split(ra[i][e], l);
-#pragma unroll
-                for (int q = 0; q < P; ++q) w[q][e >> 2] |= l[q] << (8 * (e & 3));
-            }
-#pragma unroll
-            for (int q = 0; q < P; ++q) {
-                uint32_t* dst = (uint32_t*)&As[buf][q][row][swz8(row, e8 >> 1)];
-                dst[(e8 & 1) * 2 + 0] = w[q][0];
-                dst[(e8 & 1) * 2 + 1] = w[q][1];
-            }
-        }
-#pragma unroll
-        for (int c = 0; c < BWN; ++c) {
-            const int col = bnb * BWN + c;
-            uint32_t w[P] = {};
-#pragma unroll
-            for (int r = 0; r < 4; ++r) {
-                uint32_t l[P];
-                S::split(rb[r][c], l);
-#pragma unroll
-                for (int q = 0; q < P; ++q) w[q] |= l[q] << (8 * r);
-            }
-#pragma unroll
-            for (int q = 0; q < P; ++q) {
-                uint32_t* dst = (uint32_t*)&Bs[buf][q][col][swz8(col, bkb >> 2)];
-                dst[bkb & 3] = w[q];
-            }
-        }
-    };
-
-    i16x acc[G][TM][TN];
-#pragma unroll
-    for (int g = 0; g < G; ++g)
-#pragma unroll
-        for (int i = 0; i < TM; ++i)
-#pragma unroll
-            for (int j = 0; j < TN; ++j) acc[g][i][j] = i16x{};
-
-    const int ktiles = (p.K + BK - 1) / BK;
-    load(0);
-    stash(0);
-    __syncthreads();
-    for (int t = 0; t < ktiles; ++t) {
-        const int buf = t & 1;
-        if (t + 1 < ktiles) load((t + 1) * BK);
-#pragma unroll
-        for (int ks = 0; ks < BK / 32; ++ks) {
-            const int c = ks * 2 + (lane >> 5);
-            i4 a[P][TM], bv[P][TN];
-#pragma unroll
-            for (int q = 0; q < P; ++q) {
-#pragma unroll
-                for (int i = 0; i < TM; ++i) {
-                    const int row = wm * WM + i * 32 + (lane & 31);
-                    a[q][i] = As[buf][q][row][swz8(row, c)];
-                }
-#pragma unroll
-                for (int j = 0; j < TN; ++j) {
-                    const int col = wn * WN + j * 32 + (lane & 31);
-                    bv[q][j] = Bs[buf][q][col][swz8(col, c)];
-                }
-            }
-#pragma unroll
-            for (int pr = 0; pr < S::PRODUCTS; ++pr)
-#pragma unroll
-                for (int i = 0; i < TM; ++i)
-#pragma unroll
-                    for (int j = 0; j < TN; ++j)
-                        acc[S::pg[pr]][i][j] = __builtin_amdgcn_mfma_i32_32x32x32_i8(
-                            a[S::pa[pr]][i], bv[S::pb[pr]][j], acc[S::pg[pr]][i][j], 0, 0, 0);
-        }
-        if (t + 1 < ktiles) stash(buf ^ 1);
-        __syncthreads();
-    }
-
-    const uint32_t cc = (uint32_t)p.corr_c;
-    const uint32_t kcc = (uint32_t)p.K * cc * cc;
-    const int32_t* rs = p.rowsum ? p.rowsum + (int64_t)b * p.M : nullptr;
-    // column sums arrive as cs_slices partial rows [slice][N]
-    const int32_t* cs = p.colsum ? p.colsum + (int64_t)b * p.cs_slices * p.N : nullptr;
-#pragma unroll
-    for (int j = 0; j < TN; ++j) {
-        const int gn = n0 + wn * WN + j * 32 + (lane & 31);
-        if (gn >= p.N) continue;
-        uint32_t csum = 0;
-        if (cc)
-            for (int s = 0; s < p.cs_slices; ++s) csum += (uint32_t)cs[(int64_t)s * p.N + gn];
-#pragma unroll
-        for (int i = 0; i < TM; ++i)
-#pragma unroll
-            for (int r = 0; r < 16; ++r) {
-                const int gm = m0 + wm * WM + i * 32 + 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3);
-                if (gm >= p.M) continue;
-                uint32_t g[G];
-#pragma unroll
-                for (int q = 0; q < G; ++q) g[q] = (uint32_t)acc[q][i][j][r];
-                uint32_t v = S::combine(g);
-                if (cc) v += cc * ((uint32_t)rs[gm] + csum) - kcc;
-                store_c(p, C, gm, gn, v);
-            }
-    }
-}
-
-// ===========================================================================
-// int8 limb routes for large problems: encode to limb planes, then an NT
-// int8 GEMM staged global -> LDS with global_load_lds_dwordx4.
-// ===========================================================================
 // smul24 limbs of four operands packed per plane with byte permutes: the
 // dword of plane q holds limb q of u0..u3 in bytes 0..3.  Limb q is byte q
 // of (x mod 2^24) ^ 0x008080 (bytes 0 and 1 flipped by 0x80), so the padding
@@ -623,6 +501,182 @@ __device__ __forceinline__ uint32_t pack4(const T* x, const bool* ok, uint32_t* 
     return sum;
 }
 
+// 64-byte LDS rows (BK = 64 int8) as four 16-byte chunks; the swizzle keeps
+// the eight rows of one ds_read_b128 pass in distinct banks.
+__device__ __forceinline__ int swz8(int row, int c) { return c ^ ((row >> 1) & 3); }
+
+template <class S, class T, int BM, int BN, int WM, int WN>
+__global__ __launch_bounds__(NT) void k_gemm_i8limb(const GemmParams p) {
+    constexpr int BK = 64, KCH = 4;
+    constexpr int P = S::PLANES, G = S::GROUPS;
+    constexpr int TM = WM / 32, TN = WN / 32;
+    constexpr int WAVES_N = BN / WN;
+    static_assert((BM / WM) * (BN / WN) == 4, "four waves");
+    constexpr int A_VECS = BM * BK / 8 / NT;      // 8-element A vectors per thread
+    constexpr int BWN = BN / 16;                  // B staged as 4(k) x BWN(n) blocks
+    static_assert((BK / 4) * (BN / BWN) == NT, "one B block per thread");
+
+    constexpr bool OFFS = S::PAD != 0;
+    __shared__ i4 As[2][P][BM][KCH];
+    __shared__ i4 Bs[2][P][BN][KCH];
+    // offset schemes: c rowsum - K c^2 of the tile's rows, c colsum of its columns
+    __shared__ uint32_t corr_m[BM], corr_n[BN];
+
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int wm = wave / WAVES_N, wn = wave % WAVES_N;
+    const int tiles_m = (p.M + BM - 1) / BM;
+    int tm, tn;
+    tile_coords(tiles_m, p.tiles_n, tm, tn);
+    const int m0 = tm * BM, n0 = tn * BN;
+    const int b = blockIdx.z;
+    const T* A = (const T*)p.A + b * p.sA;
+    const T* B = (const T*)p.B + b * p.sB;
+    int32_t* C = (int32_t*)p.C + b * p.sC;
+
+    T ra[A_VECS][8];
+    T rb[4][BWN];
+    const int bkb = tid / (BN / BWN), bnb = tid % (BN / BWN);
+
+    // Rows and columns past the operands repeat the last ones (their outputs
+    // are not stored); k past K is all-zero limbs in A, so B's there may be
+    // anything.
+    auto load = [&](int k0) {
+#pragma unroll
+        for (int i = 0; i < A_VECS; ++i) {
+            const int v = tid + NT * i, row = v / 8, gk = k0 + v % 8 * 8;
+            load_row(A + (int64_t)min(m0 + row, p.M - 1) * p.lda, gk, p.K, ra[i]);
+            if (k0 + BK > p.K) {
+#pragma unroll
+                for (int e = 0; e < 8; ++e)
+                    if (gk + e >= p.K) ra[i][e] = (T)S::PAD;
+            }
+        }
+#pragma unroll
+        for (int r = 0; r < 4; ++r)
+            load_row(B + (int64_t)min(k0 + bkb * 4 + r, p.K - 1) * p.ldb, n0 + bnb * BWN, p.N, rb[r]);
+    };
+    auto stash = [&](int buf) {
+        const bool all[4] = {true, true, true, true};
+#pragma unroll
+        for (int i = 0; i < A_VECS; ++i) {
+            const int v = tid + NT * i, row = v / 8, e8 = v % 8;
+            uint32_t w[2][P];
+            pack4<S, T>(&ra[i][0], all, w[0]);
+            pack4<S, T>(&ra[i][4], all, w[1]);
+#pragma unroll
+            for (int q = 0; q < P; ++q) {
+                uint32_t* dst = (uint32_t*)&As[buf][q][row][swz8(row, e8 >> 1)];
+                *(u2*)&dst[(e8 & 1) * 2] = u2{w[0][q], w[1][q]};
+            }
+        }
+#pragma unroll
+        for (int c = 0; c < BWN; ++c) {
+            const int col = bnb * BWN + c;
+            const T x[4] = {rb[0][c], rb[1][c], rb[2][c], rb[3][c]};
+            uint32_t w[P];
+            pack4<S, T>(x, all, w);
+#pragma unroll
+            for (int q = 0; q < P; ++q) {
+                uint32_t* dst = (uint32_t*)&Bs[buf][q][col][swz8(col, bkb >> 2)];
+                dst[bkb & 3] = w[q];
+            }
+        }
+    };
+
+    i16x acc[G][TM][TN];
+#pragma unroll
+    for (int g = 0; g < G; ++g)
+#pragma unroll
+        for (int i = 0; i < TM; ++i)
+#pragma unroll
+            for (int j = 0; j < TN; ++j) acc[g][i][j] = i16x{};
+
+    int t0, t1;
+    k_slice(p, t0, t1);
+    if (t0 >= t1) return;
+    load(t0 * BK);
+    if (OFFS && tid < BM + BN) {
+        // the offset correction, whole in the first K slice; column sums
+        // arrive as cs_slices partial rows [slice][N]
+        const uint32_t cc = t0 == 0 ? (uint32_t)p.corr_c : 0u;
+        if (tid < BM) {
+            corr_m[tid] = cc * ((uint32_t)p.rowsum[(int64_t)b * p.M + min(m0 + tid, p.M - 1)] -
+                                (uint32_t)p.K * (uint32_t)p.corr_c);
+        } else {
+            const int32_t* cs = p.colsum + (int64_t)b * p.cs_slices * p.N + min(n0 + tid - BM, p.N - 1);
+            uint32_t sum = 0;
+            if (t0 == 0)
+                for (int s = 0; s < p.cs_slices; ++s) sum += (uint32_t)cs[(int64_t)s * p.N];
+            corr_n[tid - BM] = cc * sum;
+        }
+    }
+    stash(t0 & 1);
+    __syncthreads();
+    for (int t = t0; t < t1; ++t) {
+        const int buf = t & 1;
+        if (t + 1 < t1) load((t + 1) * BK);
+#pragma unroll
+        for (int ks = 0; ks < BK / 32; ++ks) {
+            if (t * BK + ks * 32 >= p.K) break;      // all-zero limbs
+            const int c = ks * 2 + (lane >> 5);
+            i4 a[P][TM], bv[P][TN];
+#pragma unroll
+            for (int q = 0; q < P; ++q) {
+#pragma unroll
+                for (int i = 0; i < TM; ++i) {
+                    const int row = wm * WM + i * 32 + (lane & 31);
+                    a[q][i] = As[buf][q][row][swz8(row, c)];
+                }
+#pragma unroll
+                for (int j = 0; j < TN; ++j) {
+                    const int col = wn * WN + j * 32 + (lane & 31);
+                    bv[q][j] = Bs[buf][q][col][swz8(col, c)];
+                }
+            }
+#pragma unroll
+            for (int pr = 0; pr < S::PRODUCTS; ++pr)
+#pragma unroll
+                for (int i = 0; i < TM; ++i)
+#pragma unroll
+                    for (int j = 0; j < TN; ++j)
+                        acc[S::pg[pr]][i][j] = __builtin_amdgcn_mfma_i32_32x32x32_i8(
+                            a[S::pa[pr]][i], bv[S::pb[pr]][j], acc[S::pg[pr]][i][j], 0, 0, 0);
+        }
+        if (t + 1 < t1) stash(buf ^ 1);
+        __syncthreads();
+    }
+
+    auto put = [&](auto add) {
+#pragma unroll
+        for (int j = 0; j < TN; ++j) {
+            const int col = wn * WN + j * 32 + (lane & 31), gn = n0 + col;
+            if (gn >= p.N) continue;
+            int64_t stride;
+            int32_t* c = c_column(p, C, gn, stride);
+            const uint32_t ccol = OFFS ? corr_n[col] : 0u;
+#pragma unroll
+            for (int i = 0; i < TM; ++i)
+#pragma unroll
+                for (int r = 0; r < 16; ++r) {
+                    const int row = wm * WM + i * 32 + 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3), gm = m0 + row;
+                    if (gm >= p.M) continue;
+                    uint32_t g[G];
+#pragma unroll
+                    for (int q = 0; q < G; ++q) g[q] = (uint32_t)acc[q][i][j][r];
+                    uint32_t v = S::combine(g);
+                    if (OFFS) v += ccol + corr_m[row];
+                    put_c<decltype(add)::value>(c + gm * stride, v);
+                }
+        }
+    };
+    if (p.ksplit > 1) put(std::true_type{});
+    else put(std::false_type{});
+}
+
+// ===========================================================================
+// int8 limb routes for large problems: encode to limb planes, then an NT
+// int8 GEMM staged global -> LDS with global_load_lds_dwordx4.
+// ===========================================================================
 // A [batch][M][lda] (T) -> A8 [batch][P][Mp][Kp] int8 limb planes.  One wave
 // per row (half a wave when Kp <= 512); a lane splits 16 consecutive k per
 // step.  Elements outside M x K
@@ -1336,6 +1390,34 @@ static bool aligned_for(const GemmParams& p, int elem, int bvec) {
            p.K % 8 == 0 && p.N % bvec == 0 && p.b_mode == B_KN;
 }
 
+// The register-staged kernels take 64 x 64 tiles where 128 x 128 ones would
+// be fewer than 64.
+static bool reg_staged_small(int64_t M, int64_t N, int64_t batch) {
+    return ((M + 127) / 128) * ((N + 127) / 128) * batch < 64;
+}
+
+// K slices of a register-staged kernel (grid y, added into a cleared C): one
+// workgroup takes 1.5 to 3 us per K tile, mostly waiting, so from eight K
+// tiles on, with at most 256 tiles, K is sliced until the grid has three
+// workgroups per CU (two measured up to a third slower, slices of two tiles as
+// well); the fill launch costs 2 to 4 us.  Steps, one slice / sliced: INT16
+// 23x208x5036 158 / 7.8 us, offset limbs 32x(22x20x6848) 437 / 24, smul24
+// 20x48x4096 207 / 29 and 41x208x768 46 / 12 (with the wider loads and the
+// corrections taken from LDS).  Longer K than 2^20 (which only reaches these
+// kernels past the encoders' 32-bit offsets) stays one launch.
+int reg_staged_ksplit(int32_t route, int64_t M, int64_t N, int64_t K, int64_t batch) {
+    const int64_t kt = (K + 63) / 64;
+    if (!reg_staged_small(M, N, batch) || K > (1 << 20)) return 1;
+    if (route != R_F16_EXACT && route != R_I8_DIRECT && route != R_I8_KARATSUBA && route != R_I8_OFFSET4 &&
+        route != R_S24_I8LIMB)
+        return 1;
+    const int64_t tiles = ((M + 63) / 64) * ((N + 63) / 64) * batch;
+    if (kt < 8 || tiles < 1 || tiles > 256) return 1;   // tiles 0: an empty output
+    const int64_t want = std::min(768 / tiles, kt);
+    const int64_t per = (kt + want - 1) / want;
+    return (int)((kt + per - 1) / per);   // no empty slice
+}
+
 bool build_gemm_mfma(int32_t route, const GemmParams& p, int batch, LaunchRec* rec,
                      int* tile_m, int* tile_n, int* tile_k) {
     *tile_k = 64;
@@ -1344,8 +1426,7 @@ bool build_gemm_mfma(int32_t route, const GemmParams& p, int batch, LaunchRec* r
         const bool al = aligned_for(p, 2, 8);
         const bool step = p.chunk_tiles == 0;  // chunk of 16: flush after every MFMA step
         // fewer than 64 tiles of 128 x 128: 64 x 64 tiles give 4x the workgroups
-        const int64_t tiles128 = (int64_t)((p.M + 127) / 128) * ((p.N + 127) / 128) * batch;
-        if (tiles128 < 64) {
+        if (reg_staged_small(p.M, p.N, batch)) {
             *tile_m = 64;
             *tile_n = 64;
             // K within four tiles: 32 x 32 tiles, K split over the four waves
@@ -1358,41 +1439,40 @@ bool build_gemm_mfma(int32_t route, const GemmParams& p, int batch, LaunchRec* r
                 else fill_gemm_rec(rec, k_gemm_f16_ks<false, true>, p, 32, 32, batch, "gemm_f16_ksplit_step_u");
                 return true;
             }
-            if (al && !step) fill_gemm_rec(rec, k_gemm_f16x<64, 64, 64, 32, 32, true, false>, p, 64, 64, batch, "gemm_f16x_64");
-            else if (al) fill_gemm_rec(rec, k_gemm_f16x<64, 64, 64, 32, 32, true, true>, p, 64, 64, batch, "gemm_f16x_step_64");
-            else if (!step) fill_gemm_rec(rec, k_gemm_f16x<64, 64, 64, 32, 32, false, false>, p, 64, 64, batch, "gemm_f16x_u_64");
-            else fill_gemm_rec(rec, k_gemm_f16x<64, 64, 64, 32, 32, false, true>, p, 64, 64, batch, "gemm_f16x_step_u_64");
+            if (!step) fill_gemm_rec(rec, k_gemm_f16x<64, 64, 64, 32, 32, false>, p, 64, 64, batch, "gemm_f16x_64");
+            else fill_gemm_rec(rec, k_gemm_f16x<64, 64, 64, 32, 32, true>, p, 64, 64, batch, "gemm_f16x_step_64");
+            rec->grid.y = (unsigned)std::max(p.ksplit, 1);
             return true;
         }
         *tile_m = 128;
         *tile_n = 128;
-        if (al && !step) fill_gemm_rec(rec, k_gemm_f16x<128, 128, 64, 64, 64, true, false>, p, 128, 128, batch, "gemm_f16x");
-        else if (al) fill_gemm_rec(rec, k_gemm_f16x<128, 128, 64, 64, 64, true, true>, p, 128, 128, batch, "gemm_f16x_step");
-        else if (!step) fill_gemm_rec(rec, k_gemm_f16x<128, 128, 64, 64, 64, false, false>, p, 128, 128, batch, "gemm_f16x_u");
-        else fill_gemm_rec(rec, k_gemm_f16x<128, 128, 64, 64, 64, false, true>, p, 128, 128, batch, "gemm_f16x_step_u");
+        if (!step) fill_gemm_rec(rec, k_gemm_f16x<128, 128, 64, 64, 64, false>, p, 128, 128, batch, "gemm_f16x");
+        else fill_gemm_rec(rec, k_gemm_f16x<128, 128, 64, 64, 64, true>, p, 128, 128, batch, "gemm_f16x_step");
         return true;
     }
     case R_I8_DIRECT:
     case R_I8_KARATSUBA:
     case R_I8_OFFSET4: {
-        *tile_m = 128;
-        *tile_n = 128;
-        const bool al = aligned_for(p, 2, 8);
-#define QX_I8(S, NAME)                                                                                       \
-    if (al) fill_gemm_rec(rec, k_gemm_i8limb<S, int16_t, 128, 128, 64, 64, true>, p, 128, 128, batch, NAME);  \
-    else fill_gemm_rec(rec, k_gemm_i8limb<S, int16_t, 128, 128, 64, 64, false>, p, 128, 128, batch, NAME "_u");
+        // 64 x 64 tiles while 128 x 128 ones would be fewer than 64
+        const bool small = reg_staged_small(p.M, p.N, batch);
+        *tile_m = *tile_n = small ? 64 : 128;
+#define QX_I8(S, NAME)                                                                                           \
+    if (small) fill_gemm_rec(rec, k_gemm_i8limb<S, int16_t, 64, 64, 32, 32>, p, 64, 64, batch, NAME "_64");      \
+    else fill_gemm_rec(rec, k_gemm_i8limb<S, int16_t, 128, 128, 64, 64>, p, 128, 128, batch, NAME);
         if (route == R_I8_DIRECT) { QX_I8(SchemeDirect, "gemm_i8_direct") }
         else if (route == R_I8_KARATSUBA) { QX_I8(SchemeKaratsuba, "gemm_i8_karatsuba") }
         else { QX_I8(SchemeOffset4, "gemm_i8_offset4") }
 #undef QX_I8
+        rec->grid.y = (unsigned)std::max(p.ksplit, 1);
         return true;
     }
     case R_S24_I8LIMB: {
-        *tile_m = 128;
+        const bool small = reg_staged_small(p.M, p.N, batch);
+        *tile_m = small ? 64 : 128;
         *tile_n = 64;
-        const bool al = aligned_for(p, 4, 4);
-        if (al) fill_gemm_rec(rec, k_gemm_i8limb<SchemeS24, int32_t, 128, 64, 64, 32, true>, p, 128, 64, batch, "gemm_s24_i8limb");
-        else fill_gemm_rec(rec, k_gemm_i8limb<SchemeS24, int32_t, 128, 64, 64, 32, false>, p, 128, 64, batch, "gemm_s24_i8limb_u");
+        if (small) fill_gemm_rec(rec, k_gemm_i8limb<SchemeS24, int32_t, 64, 64, 32, 32>, p, 64, 64, batch, "gemm_s24_i8limb_64");
+        else fill_gemm_rec(rec, k_gemm_i8limb<SchemeS24, int32_t, 128, 64, 64, 32>, p, 128, 64, batch, "gemm_s24_i8limb");
+        rec->grid.y = (unsigned)std::max(p.ksplit, 1);
         return true;
     }
     default:

@@ -52,8 +52,8 @@ struct GemmParams {
     int32_t tiles_n;        // number of N tiles (grid swizzle)
     int32_t cs_slices;      // colsum holds this many partial rows per batch
     int32_t bf16;           // F16_EXACT NT contraction: operands are bf16 (|x| <= 256), else fp16
-    int32_t ksplit;         // int8 NT route: K slices (grid y) added into a cleared C with
-                            // wrapping int32 atomics; <= 1: one slice, plain stores
+    int32_t ksplit;         // int8 NT route and register-staged kernels: K slices (grid y) added
+                            // into a cleared C with wrapping int32 atomics; <= 1: plain stores
     int32_t flat_batch;     // int8 NT route: batch folded into grid x (each XCD gets whole batches)
     int32_t relu;           // int8 NT route without K slices: store max(C, 0)
     int32_t pad1;
@@ -382,6 +382,7 @@ hipError_t scratch_device_ptr(int dev, void** out);
 // Integer GEMM main kernel for an MFMA route; returns false if unsupported.
 bool build_gemm_mfma(int32_t route, const GemmParams& p, int batch, LaunchRec* rec,
                      int* tile_m, int* tile_n, int* tile_k);
+int reg_staged_ksplit(int32_t route, int64_t M, int64_t N, int64_t K, int64_t batch);
 // Row sums [batch][M] and per-slice column sums [batch][slices][N] in one launch.
 void build_sums(const SumsParams& p, LaunchRec* rec);
 int sums_slices(int K);
