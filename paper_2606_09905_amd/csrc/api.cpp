@@ -227,7 +227,18 @@ static bool skinny_s24(const GemmSpec& s) {
 qx_status plan_int_gemm(const GemmSpec& s, Plan* pl, uint64_t* ws_used) {
     int32_t route = s.route;
     if (!s.s24) {
-        if (route == R_AUTO) route = auto_i16(s.ba, s.bb);
+        if (route == R_AUTO) {
+            route = auto_i16(s.ba, s.bb);
+            // A chunk under one K tile flushes the fp32 sums after every MFMA
+            // step, four times the step's own cycles, and has no encoded
+            // path: large problems take three int8 products instead (bounds
+            // 1024, 3x(2435x528x4671) 672 / 224 us, 1000x777x500 22.1 / 15.3;
+            // below the line 512^3 10.8 / 12.2, 2048x2048x128 13.0 / 14.3).
+            if (route == R_F16_EXACT && f16_chunk(s.ba, s.bb) < 64 && feasible_i16(R_I8_KARATSUBA, s.ba, s.bb) &&
+                s.allow_nt && s.K >= 256 && use_i8nt(R_I8_KARATSUBA, s.M, s.N, s.K, s.batch) &&
+                (double)s.M * (double)s.N * (double)s.K * (double)s.batch >= (double)(1 << 28))
+                route = R_I8_KARATSUBA;
+        }
         if (!route_applies_i16(route))
             return fail(QX_ERR_INVALID_ARG, "route %d does not apply to an int16 contraction", route);
         if (!feasible_i16(route, s.ba, s.bb))
@@ -916,7 +927,12 @@ qx_status plan_conv_t(Plan* pl, int32_t dt, int64_t N, int64_t Ci, int64_t H, in
     const bool gather = (route == R_AUTO || route == R_S24_I8LIMB) && use_i8nt(R_S24_I8LIMB, Co, P, Kd, 1);
     // few output channels: a direct vector-ALU kernel (a GEMM tile would be
     // mostly empty)
-    const bool direct = Co <= 16 && Kd <= 1024 && KW <= 8 && (route == R_S24_VALU || (route == R_AUTO && !gather));
+    // (a thread walks all of C_in*KH*KW, so long sums want pixels enough to
+    // hide it: 13x256x25x24 -> 16 1x1 429 us against 33 through the limbs,
+    // 2x16x28x28 3x3 53 / 20, 32x32x56x56 3x3 146 / 155, 8x1x32x32 -> 6 5x5
+    // 10.0 / 11.5)
+    const bool direct = Co <= 16 && Kd <= 1024 && KW <= 8 &&
+                        (route == R_S24_VALU || (route == R_AUTO && !gather && (Kd <= 48 || P >= (1 << 16))));
     if (direct) {
         info.route = R_S24_VALU;
         info.products = 1;

@@ -1391,9 +1391,9 @@ static bool aligned_for(const GemmParams& p, int elem, int bvec) {
 }
 
 // The register-staged kernels take 64 x 64 tiles where 128 x 128 ones would
-// be fewer than 64.
+// be fewer than 64 or more than half empty.
 static bool reg_staged_small(int64_t M, int64_t N, int64_t batch) {
-    return ((M + 127) / 128) * ((N + 127) / 128) * batch < 64;
+    return M <= 64 || N <= 64 || ((M + 127) / 128) * ((N + 127) / 128) * batch < 64;
 }
 
 // K slices of a register-staged kernel (grid y, added into a cleared C): one

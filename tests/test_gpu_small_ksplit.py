@@ -79,3 +79,28 @@ def test_empty_output_of_a_long_sum():
     for M, N in ((0, 5), (5, 0)):
         assert qx.plan_gemm_i16i32(M, N, 4096, 1, 127, 127)["kernels"] == 0
         assert qx.plan_gemm_i32_s24(M, N, 4096)["kernels"] == 0
+
+
+@pytest.mark.parametrize("N,Ci,H,W,Co,k,stride", [(2, 16, 9, 11, 16, 3, 1), (1, 48, 6, 5, 3, 1, 1), (1, 49, 6, 5, 3, 1, 2),
+                                                  (3, 60, 7, 7, 15, 4, 1)])
+def test_conv_i32_few_channels(N, Ci, H, W, Co, k, stride):
+    # long sums over few pixels go through the limbs, short ones stay direct
+    rng = np.random.default_rng(Ci)
+    x = ints(rng, (N, Ci, H, W), -(1 << 23), (1 << 23) - 1, np.int32)
+    w = ints(rng, (Co, Ci, k, k), -(1 << 23), (1 << 23) - 1, np.int32)
+    auto = qx.conv2d_gemm_t(torch.from_numpy(x).cuda(), torch.from_numpy(w).cuda(), stride, k // 2)
+    with qx.Executor.conv2d_t("i32", N, Ci, H, W, Co, k, k, stride, k // 2, "s24_valu") as ex:
+        direct = ex.run([torch.from_numpy(x).cuda(), torch.from_numpy(w).cuda()])
+        torch.cuda.synchronize()
+    assert torch.equal(auto, direct)
+    assert np.array_equal(auto.cpu().numpy(), orc.conv2d_s24(x, w, stride, k // 2))
+
+
+@pytest.mark.parametrize("M,N,K", [(1024, 1024, 257), (700, 801, 500)])
+def test_flushing_bounds_large(M, N, K):
+    # bounds whose chunk is under one K tile: three int8 products when large
+    assert qx.plan_gemm_i16i32(M, N, K, 1, 1024, 1024)["route_name"] == "i8_karatsuba"
+    rng = np.random.default_rng(K)
+    A, B = ints(rng, (1, M, K), -1024, 1024, np.int16), ints(rng, (1, K, N), -1024, 1024, np.int16)
+    C = run(qx.Executor.gemm_i16i32(M, N, K, 1, 1024, 1024), A, B)
+    assert np.array_equal(C, orc.gemm_i16i32(A, B))
