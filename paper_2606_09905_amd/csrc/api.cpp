@@ -502,24 +502,20 @@ qx_status plan_int_gemm(const GemmSpec& s, Plan* pl, uint64_t* ws_used) {
         const uint64_t a_off = round_up(*ws_used, 256);
         const uint64_t b_off = round_up(a_off + (uint64_t)s.batch * P * Mp * Kp, 256);
         *ws_used = b_off + (uint64_t)s.batch * P * Np * Kp;
-        const int64_t v16 = s.s24 ? 4 : 8;   // elements per 16 bytes
         EncPairParams ep{};
         EncParams& ea = ep.a;
         ea.s_src = s.sA; ea.s_dst = P * Mp * Kp;
         ea.M = (int32_t)s.M; ea.K = (int32_t)s.K;
         ea.Mp = (int32_t)Mp; ea.Kp = (int32_t)Kp;
         ea.ld_src = (int32_t)s.lda; ea.batch = (int32_t)s.batch;
-        ea.vec = (s.lda % v16 == 0 && s.sA % v16 == 0) ? 1 : 0;
         EncParams& eb = ep.b;
         eb.s_src = s.sB; eb.s_dst = P * Np * Kp;
         eb.N = (int32_t)s.N; eb.K = (int32_t)s.K;
         eb.Np = (int32_t)Np; eb.Kp = (int32_t)Kp;
         eb.ld_src = (int32_t)s.ldb; eb.batch = (int32_t)s.batch;
-        eb.vec = (s.ldb % 4 == 0 && s.sB % 4 == 0) ? 1 : 0;
         if (s.b_conv) {
             eb.conv = 1;
             eb.g = s.geo;
-            eb.vec = 0;
         }
         LaunchRec r1;
         build_enc_limb(route, s.s24, ep, &r1);

@@ -447,18 +447,6 @@ struct SchemeS24 {  // smul24: u = sext24(x) + 2^23, s_i = byte_i(u) - 128, x = 
     }
 };
 
-// Aligned vector load of N elements (whole 16-byte transactions).
-template <class T, int N>
-struct alignas(N * sizeof(T) >= 16 ? 16 : N * sizeof(T)) VecN {
-    T v[N];
-};
-template <class T, int N>
-__device__ __forceinline__ void load_vec(const T* src, T (&dst)[N]) {
-    const VecN<T, N> x = *(const VecN<T, N>*)src;
-#pragma unroll
-    for (int e = 0; e < N; ++e) dst[e] = x.v[e];
-}
-
 // smul24 limbs of four operands packed per plane with byte permutes: the
 // dword of plane q holds limb q of u0..u3 in bytes 0..3.  Limb q is byte q
 // of (x mod 2^24) ^ 0x008080 (bytes 0 and 1 flipped by 0x80), so the padding
@@ -702,8 +690,8 @@ __device__ __forceinline__ void enc_limb_a(const EncParams& p, int blk) {
     for (int k0 = lane * 16; k0 < p.Kp; k0 += LW * 16) {
         T x[16];
         bool ok[16];
-        if (p.vec && m < p.M && k0 + 16 <= p.K) {
-            load_vec<T, 16>(src + k0, x);
+        if (m < p.M && k0 + 16 <= p.K) {
+            load_row(src, k0, p.K, x);
 #pragma unroll
             for (int e = 0; e < 16; ++e) ok[e] = true;
         } else {
@@ -730,7 +718,7 @@ __device__ __forceinline__ void enc_limb_a(const EncParams& p, int blk) {
 // 64(k) x 64(n) block.  A thread takes four k rows of four columns, packs
 // the four k bytes of each column and plane into one dword and stages it in
 // LDS; the rows then leave as 16-byte runs along k.  Plain B: a thread's
-// columns are consecutive (one 16-byte load per row).  Conv (B gathered
+// columns are consecutive (one vector load per row, at any alignment).  Conv (B gathered
 // from the NCHW input, k = (ci*KH + kh)*KW + kw, n = (img*Ho + oh)*Wo + ow):
 // a thread's columns are 16 apart so that 16 lanes gather 16 consecutive
 // pixels, and the workgroup first tabulates its 64 rows' tap offsets and its
@@ -803,8 +791,8 @@ __device__ __forceinline__ void enc_limb_bt(const EncParams& p, int blk) {
         for (int r = 0; r < 4; ++r) {
             const int k = kb + r;
             const T* row = src + (int64_t)k * p.ld_src + nb;
-            if (p.vec && k < p.K && nb + 4 <= p.N) {
-                load_vec<T, 4>(row, x[r]);
+            if (k < p.K && nb + 4 <= p.N) {
+                load_row(row, 0, 4, x[r]);
 #pragma unroll
                 for (int c = 0; c < 4; ++c) ok[r][c] = true;
             } else {
