@@ -2324,14 +2324,21 @@ qx_status qgemm_i16i32_noalloc(const int16_t* A, const int16_t* B, int32_t* C, i
         auto it = g_noalloc_plans->find(key);
         if (it == g_noalloc_plans->end()) {
             Plan p;
-            qx_status st = plan_gemm(&p, false, M, N, K, batch, bound_a, bound_b, R_AUTO);
+            // the bounds' own route, whatever the size: the route a large
+            // problem takes instead of fp16 with a short chunk would use the
+            // scratch array, which such calls do not share otherwise
+            int64_t ba = 0, bb = 0;
+            qx_status st = check_bound16(bound_a, "bound_a", &ba);
+            if (!st) st = check_bound16(bound_b, "bound_b", &bb);
+            const int32_t route = st ? R_AUTO : auto_i16(ba, bb);
+            st = plan_gemm(&p, false, M, N, K, batch, bound_a, bound_b, route);
             if (st) return st;
             if (scratch_need(p) > kScratchBytes) {
                 // the encoded operands do not fit: the register-staged
                 // kernels convert while staging and need only the row and
                 // column sums of the offset routes
                 Plan q;
-                if ((st = plan_gemm(&q, false, M, N, K, batch, bound_a, bound_b, R_AUTO, false))) return st;
+                if ((st = plan_gemm(&q, false, M, N, K, batch, bound_a, bound_b, route, false))) return st;
                 p = std::move(q);
             }
             if (scratch_need(p) > kScratchBytes)

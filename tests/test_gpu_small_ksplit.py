@@ -51,13 +51,13 @@ def test_s24(b, M, N, K):
     assert np.array_equal(C, orc.gemm_i32_s24(A, B))
 
 
-@pytest.mark.parametrize("K", [449, 1500])
-def test_no_alloc_call(K):
+@pytest.mark.parametrize("M,N,K,bound", [(50, 70, 449, 256), (50, 70, 1500, 256), (700, 801, 500, 1024)])
+def test_no_alloc_call(M, N, K, bound):
     rng = np.random.default_rng(K)
-    A, B = ints(rng, (50, K), -256, 255, np.int16), ints(rng, (K, 70), -256, 255, np.int16)
+    A, B = ints(rng, (M, K), -bound, bound - 1, np.int16), ints(rng, (K, N), -bound, bound - 1, np.int16)
     a, b = torch.from_numpy(A).cuda(), torch.from_numpy(B).cuda()
-    C = torch.full((50, 70), 7, dtype=torch.int32, device="cuda")
-    qx.check(qx.lib().qgemm_i16i32_noalloc(a.data_ptr(), b.data_ptr(), C.data_ptr(), 50, 70, K, 1, 256, 256,
+    C = torch.full((M, N), 7, dtype=torch.int32, device="cuda")
+    qx.check(qx.lib().qgemm_i16i32_noalloc(a.data_ptr(), b.data_ptr(), C.data_ptr(), M, N, K, 1, bound, bound,
                                            torch.cuda.current_stream().cuda_stream))
     torch.cuda.synchronize()
     assert np.array_equal(C.cpu().numpy(), orc.gemm_i16i32(A, B))
