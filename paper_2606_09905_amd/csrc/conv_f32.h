@@ -272,17 +272,26 @@ __global__ __launch_bounds__(BM * BN / WN) void k_conv_f32(const ConvF32Params p
             const float* xi = p.x + (int64_t)n_img * g.Ci * g.H * g.W;
             acc[0][j] = f16x{};
             acc[1][j] = f16x{};
-            for (int k0 = tile0 * 32; k0 < (tile0 + ktiles) * 32; k0 += 2) {
-                const int k = k0 + hh, tap = k / g.Ci, ci = k - tap * g.Ci, kh = tap / g.KW, kw = tap - kh * g.KW;
-                const int ih = oh * g.stride + kh - g.pad, iw = ow * g.stride + kw - g.pad;
-                const bool in = ih >= 0 && ih < g.H && iw >= 0 && iw < g.W;
-                const float bv = in ? xi[((int64_t)ci * g.H + ih) * g.W + iw] : 0.f;
+            // 16 k at a time, their loads in flight together
+            for (int k0 = tile0 * 32; k0 < (tile0 + ktiles) * 32; k0 += 16) {
+                float bv[8], av[2][8];
 #pragma unroll
-                for (int i = 0; i < 2; ++i) {
-                    const int gm = m0 + wm * 64 + i * 32 + l32;
-                    const float av = gm < p.Co ? p.w[((int64_t)gm * g.Ci + ci) * taps + tap] : 0.f;
-                    acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(av, bv, acc[i][j], 0, 0, 0);
+                for (int e = 0; e < 8; ++e) {
+                    const int k = k0 + 2 * e + hh, tap = k / g.Ci, ci = k - tap * g.Ci, kh = tap / g.KW, kw = tap - kh * g.KW;
+                    const int ih = oh * g.stride + kh - g.pad, iw = ow * g.stride + kw - g.pad;
+                    const bool in = ih >= 0 && ih < g.H && iw >= 0 && iw < g.W;
+                    bv[e] = in ? xi[((int64_t)ci * g.H + ih) * g.W + iw] : 0.f;
+#pragma unroll
+                    for (int i = 0; i < 2; ++i) {
+                        const int gm = m0 + wm * 64 + i * 32 + l32;
+                        av[i][e] = gm < p.Co ? p.w[((int64_t)gm * g.Ci + ci) * taps + tap] : 0.f;
+                    }
                 }
+#pragma unroll
+                for (int e = 0; e < 8; ++e)
+#pragma unroll
+                    for (int i = 0; i < 2; ++i)
+                        acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(av[i][e], bv[e], acc[i][j], 0, 0, 0);
             }
         }
         if (gn >= p.P) continue;
