@@ -87,11 +87,11 @@ typedef enum {
     QX_ROUTE_VALU_DOT2 = 5,
     QX_ROUTE_S24_VALU = 6,
     QX_ROUTE_S24_I8LIMB = 7,
-    QX_ROUTE_ATTN_F32_MFMA = 8,  /* attention: FP32 as six bf16 MFMA products, S tile kept on chip */
+    QX_ROUTE_ATTN_F32_MFMA = 8,  /* attention: FP32 as eight bf16 MFMA products, S tile kept on chip */
     QX_ROUTE_ATTN_I32_MFMA = 9,  /* attention: int8 MFMA for QK^T, S split into int8 limbs */
     QX_ROUTE_ATTN_I32_VALU = 10, /* attention: vector-ALU int32, any operand range */
     QX_ROUTE_ATTN_F32_VALU = 11, /* attention: vector-ALU fp32 (d outside the MFMA shapes) */
-    QX_ROUTE_F32_MFMA = 12,      /* FP32 conv: six bf16 MFMA products (C_in a multiple of 32) */
+    QX_ROUTE_F32_MFMA = 12,      /* FP32 conv: eight bf16 MFMA products (C_in a multiple of 32) */
     QX_ROUTE_F32_VALU = 13       /* FP32 conv: vector-ALU fp32, any shape */
 } qx_route;
 

@@ -1,6 +1,6 @@
 // conv_f32.h -- FP32 convolution (Methodology, Table 2: the FP32 Conv2D row)
 // on the bf16 matrix cores, C_in a multiple of 32: every float as three bf16
-// terms, six products kept (f32_split.h).  Compiled as a part of
+// terms, eight products kept (f32_split.h).  Compiled as a part of
 // k_gemm_nt.hip.
 //
 //  1. Prep: x NCHW -> a zero-bordered NHWC image of split values,
@@ -15,16 +15,15 @@
 //     fp32 matrix cores from x and w.  Few tiles split K over workgroups; the
 //     partial outputs are added in split order.
 //
-// Bound (8x64x56x56 -> 128, 3x3): 392 tiles on 256 CUs, so 13 us of matrix
-// products on the busiest SIMDs; the kernel takes 24 to 26 us.  Working copies
-// of a 128 x 128 tile: without the products 17 us, without the loads 24,
-// without the LDS reads 24.5, products alone 22 (launch, first tile and 12.8 MB
-// of output included), so the products bound it.  Tiles of 128 x 128 (eight
-// waves, three stages) took the same time there and lose where C_out is not a
-// multiple of 128; six stages of 64 x 64 gained nothing over two.
+// Bound (8x64x56x56 -> 128, 3x3): 392 tiles on 256 CUs, so 17 us of matrix
+// products on the busiest SIMDs; the kernel takes about 31 us of the 38 (46 on
+// the fp32 matrix cores).  Tiles of 128 x 128 (eight waves, three stages) and
+// six stages of 64 x 64 gained nothing there (measured with six products a
+// multiply-add), and the former lose where C_out is not a multiple of 128.
 #pragma once
 
 #include <algorithm>
+#include <type_traits>
 
 #include "f32_split.h"
 #include "qx_internal.h"
@@ -186,11 +185,11 @@ __global__ __launch_bounds__(BM * BN / WN) void k_conv_f32(const ConvF32Params p
         bb = p.xs + (int64_t)(tap_h * Wp + tap_w) * pix_bytes + tap_c;
     };
 
-    f16x acc[2][TN];
+    f16x acc[2][TN], low[2][TN];   // sums of the h h products and of the smaller ones
 #pragma unroll
     for (int i = 0; i < 2; ++i)
 #pragma unroll
-        for (int j = 0; j < TN; ++j) acc[i][j] = f16x{};
+        for (int j = 0; j < TN; ++j) acc[i][j] = low[i][j] = f16x{};
     struct Frag {
         b8 a[2][3], b[TN][3];
     };
@@ -211,11 +210,13 @@ __global__ __launch_bounds__(BM * BN / WN) void k_conv_f32(const ConvF32Params p
 #pragma unroll
         for (int i = 0; i < 2; ++i)
 #pragma unroll
-            for (int j = 0; j < TN; ++j)
-                acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(f.a[i][pa], f.b[j][pb], acc[i][j], 0, 0, 0);
+            for (int j = 0; j < TN; ++j) {
+                f16x& sum = pa + pb ? low[i][j] : acc[i][j];
+                sum = __builtin_amdgcn_mfma_f32_32x32x16_bf16(f.a[i][pa], f.b[j][pb], sum, 0, 0, 0);
+            }
     };
     // smallest products first
-    constexpr int PA[6] = {2, 1, 0, 1, 0, 0}, PB[6] = {0, 1, 2, 0, 1, 0};
+    constexpr int TERMS = 8, PA[TERMS] = {2, 1, 2, 1, 0, 1, 0, 0}, PB[TERMS] = {1, 2, 0, 1, 2, 0, 1, 0};
 
     // Each 16-k step's fragments are read while the step before is
     // multiplied, and a tile's loads are issued between the products of the
@@ -232,29 +233,34 @@ __global__ __launch_bounds__(BM * BN / WN) void k_conv_f32(const ConvF32Params p
     __syncthreads();
     Frag f0, f1;
     read(0, 0, f0);
-    for (int t = 0; t < ktiles; ++t) {
+    // (tile t of those with a tile t + STAGES to load: `more`)
+    auto step = [&](int t, auto more) {
         read(t, 1, f1);
 #pragma unroll
-        for (int e = 0; e < 6; ++e) term(f0, PA[e], PB[e]);
-        if (t + 1 == ktiles) break;
+        for (int e = 0; e < TERMS; ++e) term(f0, PA[e], PB[e]);
         // tile t + 1 has landed
         if (t + STAGES - 1 < ktiles) wait_loads<(STAGES - 2) * LPT>();
         else wait_loads<0>();
         __syncthreads();
         read(t + 1, 0, f0);
-        const bool more = t + STAGES < ktiles;
 #pragma unroll
-        for (int e = 0; e < 6; ++e) {
+        for (int e = 0; e < TERMS; ++e) {
             term(f1, PA[e], PB[e]);
-            if (more) {
+            if constexpr (decltype(more)::value) {
 #pragma unroll
-                for (int i = e * LPT / 6; i < (e + 1) * LPT / 6; ++i) load(t + STAGES, i);
+                for (int i = e * LPT / TERMS; i < (e + 1) * LPT / TERMS; ++i) load(t + STAGES, i);
             }
         }
-        if (more) next();
-    }
+        if constexpr (decltype(more)::value) next();
+    };
+    int tile = 0;
+    for (; tile + STAGES < ktiles; ++tile) step(tile, std::true_type{});
+    for (; tile + 1 < ktiles; ++tile) step(tile, std::false_type{});
+    read(tile, 1, f1);
 #pragma unroll
-    for (int e = 0; e < 6; ++e) term(f1, PA[e], PB[e]);
+    for (int e = 0; e < TERMS; ++e) term(f0, PA[e], PB[e]);
+#pragma unroll
+    for (int e = 0; e < TERMS; ++e) term(f1, PA[e], PB[e]);
 
     const int taps = g.KH * g.KW;
     float* out = p.part ? p.part + (int64_t)blockIdx.y * p.part_stride : p.y;
@@ -266,7 +272,10 @@ __global__ __launch_bounds__(BM * BN / WN) void k_conv_f32(const ConvF32Params p
 #pragma unroll
         for (int i = 0; i < 2; ++i)
 #pragma unroll
-            for (int r = 0; r < 16; ++r) nan |= acc[i][j][r] != acc[i][j][r];
+            for (int r = 0; r < 16; ++r) {
+                acc[i][j][r] += low[i][j][r];
+                nan |= acc[i][j][r] != acc[i][j][r];
+            }
         if (__ballot(nan && gn < p.P) != 0) {
             const int oh = n_pix / g.Wo, ow = n_pix - oh * g.Wo;
             const float* xi = p.x + (int64_t)n_img * g.Ci * g.H * g.W;

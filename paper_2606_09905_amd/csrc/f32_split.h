@@ -1,15 +1,16 @@
 // f32_split.h -- FP32 products on the bf16 matrix cores.
 //
 // A float of 24 significant bits is the exact sum of three bf16 values,
-// x = h + m + l with |m| <= 2^-9 |x| and |l| <= 2^-18 |x| (each the rounding
-// of what the ones before it leave).  A product keeps the six terms down to
-// 2^-18 of it (l l, l m and m l, below 2^-26, are under the fp32 rounding),
-// summed in the MFMA's fp32 accumulator, smallest terms first.  Six
-// v_mfma_f32_32x32x16_bf16 (32 cycles each, 16 k) replace eight
-// v_mfma_f32_32x32x2f32 (64 cycles each): 192 against 512 cycles.  The error
-// is no larger: one such step over 16 products rounds to 0.41 ulp rms of the
-// running sum where eight fp32 steps gave 0.92 to 1.16 (measured), and its
-// mean is 0 as theirs.
+// x = h + m + l with |m| <= 2^-8 |x| and |l| <= 2^-17 |x| (each the rounding
+// of what the ones before it leave: the published three-term bf16 split).  Of
+// the nine products of two such sums all but l l are kept, which is at most
+// 2^-34 of the whole: a product is exact to a thousandth of fp32's rounding.
+// Eight v_mfma_f32_32x32x16_bf16 (32 cycles each, 16 k) replace eight
+// v_mfma_f32_32x32x2f32 (64 cycles each).
+//
+// The h h products are summed apart from the smaller ones (or after them):
+// each step rounds its running sum, and only theirs is of full size, one
+// rounding for 16 products where the fp32 cores round for every two.
 //
 // The split is exact, and no product overflows, for x = 0 or
 // 2^ELO <= |x| < 2^EHI; SplitRange notes a value outside (infinities and NaN

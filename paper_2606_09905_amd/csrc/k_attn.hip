@@ -666,13 +666,14 @@ __global__ __launch_bounds__(512) void k_attn_i32s(const AttnParams p) {
 // never change lanes.  One barrier per block; a block's loads are in flight
 // for a whole block before it is staged.
 //
-// Bound: the matrix cores' power.  16 heads x 4096 x 64, softmax: 344 us
-// (590 us on v_mfma_f32_32x32x2f32), matrix cores busy 65% of the cycles at
-// 1.74 GHz; per 32x32 block and wave 1536 matrix cycles against about 1250 of
-// vector ALU (exponentials, splits).  Without the software pipeline (PIPE,
-// which d >= 96 has no registers for: d = 128 measured 237 us with it and
-// spills, 200 without) the two waves of a SIMD meet in their vector phases:
-// 363 us, 51% busy.  The core at L = 4096, d = 64: 36 us (40 us before).
+// Bound: the matrix cores; per 32x32 block and wave 2048 matrix cycles against
+// about 1450 of vector ALU (exponentials, splits).  32 causal heads x 4096 x
+// 64: 444 us, d = 128, 16 x 2048: 243 (616 and 302 on v_mfma_f32_32x32x2f32);
+// the core at L = 4096, d = 64 40 us (43); errors a third of theirs.  Without
+// the products m l and l m and with one running sum (338, 195 and 33 us) a
+// sum of one product was up to 1.4 ulp off.  The software pipeline (PIPE) is
+// the core's for d <= 64: the softmax form measured 4% slower with it, and
+// d >= 96 has no registers for it.
 //
 // Softmax: per block the running maximum m (base-2 exponent domain,
 // t = scale*log2(e)*s) and the running sum are updated online.  With key
@@ -691,7 +692,7 @@ __global__ __launch_bounds__(NW * 64) void k_attn_b3(const SdpaParams p) {
     constexpr int VP = 2 * AKB + 16;         // 16 rows of one chunk fall on 64 different banks)
     constexpr int KB = AKB * KP, VB = D * VP;            // bytes of one plane
     constexpr int NI = (8 * D + NTH - 1) / NTH;          // staging items (8 elements) per thread
-    constexpr bool PIPE = D <= 64;
+    constexpr bool PIPE = !SM && D <= 64;
     // products of the core reach |q k| d |v| L: its values are held closer to 1
     typedef SplitRange<SM ? -100 : -40, SM ? 60 : 30> Range;
     __shared__ __align__(16) unsigned char lds[2][3 * (KB + VB)];
@@ -758,9 +759,9 @@ __global__ __launch_bounds__(NW * 64) void k_attn_b3(const SdpaParams p) {
             split3(v, qh[t], qm[t], ql[t]);
         }
     }
-    f16x o[NTO];
+    f16x o[NTO], low[NTO];            // low: PIPE only
 #pragma unroll
-    for (int n = 0; n < NTO; ++n) o[n] = f16x{};
+    for (int n = 0; n < NTO; ++n) o[n] = low[n] = f16x{};
     float m = -INFINITY;              // running maximum of t for query q
     float lsum = 0.f;                 // this half's share of the running sum
 
@@ -818,21 +819,22 @@ __global__ __launch_bounds__(NW * 64) void k_attn_b3(const SdpaParams p) {
             *(b8*)(dst + 2 * plane) = l;
         }
     };
-    // S^T of block j
+    // S^T of block j: the h h products in one sum, the smaller ones in another
     auto scores = [&](int j, f16x& s) {
         const unsigned char* Ks = &lds[j & 1][l32 * KP + 16 * h];
+        f16x slow = f16x{};
         s = f16x{};
 #pragma unroll
         for (int t = 0; t < KS; ++t) {
             const b8 kh = *(const b8*)(Ks + 32 * t), km = *(const b8*)(Ks + KB + 32 * t),
                      kl = *(const b8*)(Ks + 2 * KB + 32 * t);
-            s = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kl, qh[t], s, 0, 0, 0);
-            s = __builtin_amdgcn_mfma_f32_32x32x16_bf16(km, qm[t], s, 0, 0, 0);
-            s = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kh, ql[t], s, 0, 0, 0);
-            s = __builtin_amdgcn_mfma_f32_32x32x16_bf16(km, qh[t], s, 0, 0, 0);
-            s = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kh, qm[t], s, 0, 0, 0);
-            s = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kh, qh[t], s, 0, 0, 0);
+#define QX_S(S_, K_, Q_) S_ = __builtin_amdgcn_mfma_f32_32x32x16_bf16(K_, Q_[t], S_, 0, 0, 0);
+            QX_S(slow, kl, qm) QX_S(slow, km, ql) QX_S(slow, kl, qh) QX_S(slow, km, qm) QX_S(slow, kh, ql)
+            QX_S(slow, km, qh) QX_S(slow, kh, qm) QX_S(s, kh, qh)
+#undef QX_S
         }
+        s += slow;
+        if (!PIPE) __builtin_amdgcn_sched_barrier(0);
     };
     auto scores_f32 = [&](int j, f16x& s) {
         const int key = key_lo + j * AKB + l32;
@@ -861,7 +863,7 @@ __global__ __launch_bounds__(NW * 64) void k_attn_b3(const SdpaParams p) {
                 if (8 * (r >> 2) + (r & 3) >= kl) s[r] = SM ? -INFINITY : 0.f;
         }
     };
-    float alpha = 1.f, m_use = 0.f;   // the next block's rescale factor and subtracted maximum
+    float alpha = 1.f, m_use = 0.f;   // the block's rescale factor and subtracted maximum
     auto maximum = [&](const f16x& s) {
         float mx = fmaxf(fmaxf(s[0], s[1]), s[2]);
 #pragma unroll
@@ -893,24 +895,34 @@ __global__ __launch_bounds__(NW * 64) void k_attn_b3(const SdpaParams p) {
             split3(pv, ph[t], pm[t], pl[t]);
         }
     };
-    // O^T += V^T S^T of block j; consecutive products go to different tiles
+    // O^T = alpha O^T + V^T S^T of block j.  The h h products and the smaller
+    // ones are kept apart, by the pipelined core in o and low all the way,
+    // else in sums over the block.
     auto accumulate = [&](int j, const b8 (&ph)[2], const b8 (&pm)[2], const b8 (&pl)[2]) {
         const unsigned char* Vs = &lds[j & 1][3 * KB + l32 * VP + 16 * h];
+        if (!PIPE) __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-        for (int t = 0; t < 2; ++t) {
-            b8 vh[NTO], vm[NTO], vl[NTO];
+        for (int n = 0; n < NTO; ++n) {
+            f16x high_sum = f16x{}, low_sum = f16x{};
+            f16x &hs = PIPE ? o[n] : high_sum, &ls = PIPE ? low[n] : low_sum;
+            b8 vh[2];
+#define QX_PV(S_, V_, P_) S_ = __builtin_amdgcn_mfma_f32_32x32x16_bf16(V_, P_[t], S_, 0, 0, 0);
 #pragma unroll
-            for (int n = 0; n < NTO; ++n) {
+            for (int t = 0; t < 2; ++t) {
                 const unsigned char* src = Vs + n * 32 * VP + 32 * t;
-                vh[n] = *(const b8*)src;
-                vm[n] = *(const b8*)(src + VB);
-                vl[n] = *(const b8*)(src + 2 * VB);
+                vh[t] = *(const b8*)src;
+                const b8 vm = *(const b8*)(src + VB), vl = *(const b8*)(src + 2 * VB);
+                QX_PV(ls, vl, pm) QX_PV(ls, vm, pl) QX_PV(ls, vl, ph) QX_PV(ls, vm, pm) QX_PV(ls, vh[t], pl)
+                QX_PV(ls, vm, ph) QX_PV(ls, vh[t], pm)
             }
-#define QX_PV(V_, P_) \
-            _Pragma("unroll") for (int n = 0; n < NTO; ++n) \
-                o[n] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(V_[n], P_[t], o[n], 0, 0, 0);
-            QX_PV(vl, ph) QX_PV(vm, pm) QX_PV(vh, pl) QX_PV(vm, ph) QX_PV(vh, pm) QX_PV(vh, ph)
+#pragma unroll
+            for (int t = 0; t < 2; ++t) QX_PV(hs, vh[t], ph)
 #undef QX_PV
+            if (!PIPE) {
+#pragma unroll
+                for (int r = 0; r < 16; ++r) o[n][r] = (SM ? fmaf(o[n][r], alpha, ls[r]) : o[n][r] + ls[r]) + hs[r];
+                __builtin_amdgcn_sched_barrier(0);
+            }
         }
     };
     auto accumulate_f32 = [&](int j, const f16x& s) {
@@ -926,60 +938,38 @@ __global__ __launch_bounds__(NW * 64) void k_attn_b3(const SdpaParams p) {
         }
     };
 
-    // Software pipeline: pass j splits the exponentials of block j beside the
-    // score products of block j + 1, then stages K of block j + 2 and V of
-    // block j + 1 beside the O products of block j, so each of the vector
-    // ALU's parts runs under matrix products that do not wait for it.  (The
-    // last pass's scores are of a stale block and are not used.)
-    float m_out = -INFINITY;                 // the maximum that lsum and o are relative to
+    // Software pipeline: pass j splits the scores of block j beside the score
+    // products of block j + 1, then stages K of block j + 2 and V of block
+    // j + 1 beside the O products of block j, so each of the vector ALU's
+    // parts runs under matrix products that do not wait for it.  (The last
+    // pass's scores are of a stale block and are not used.)
     Stage st;
     auto pass = [&](int j, f16x& s, f16x& sn) {
-        if (!PIPE) {
-            if (j < nact) {
-                scores(j, s);
-                mask(j, s);
-                if (SM) {
-                    maximum(s);
-                    if (__ballot(alpha != 1.f) != 0) {
-#pragma unroll
-                        for (int n = 0; n < NTO; ++n)
-#pragma unroll
-                            for (int r = 0; r < 16; ++r) o[n][r] *= alpha;
-                    }
-                    exponentials(s);
-                }
-                b8 ph[2], pm[2], pl[2];
-                split_s(s, ph, pm, pl);
-                accumulate(j, ph, pm, pl);
-            }
-            stash(st, j + 1, j + 1);
-            load(st, j + 2, j + 2);
-            __syncthreads();
-            return;
-        }
-        if (j < nact) {
-            if (SM && __ballot(alpha != 1.f) != 0) {
-#pragma unroll
-                for (int n = 0; n < NTO; ++n)
-#pragma unroll
-                    for (int r = 0; r < 16; ++r) o[n][r] *= alpha;
-            }
-            m_out = m;
-            b8 ph[2], pm[2], pl[2];
+        b8 ph[2], pm[2], pl[2];
+        if (PIPE) {
             scores(j + 1, sn);
-            if (SM) exponentials(s);
             split_s(s, ph, pm, pl);
             // all of it before the mask's branch, beside the scores
 #pragma unroll
             for (int t = 0; t < 2; ++t) asm volatile("" : "+v"(ph[t]), "+v"(pm[t]), "+v"(pl[t]));
             mask(j + 1, sn);
             accumulate(j, ph, pm, pl);
-            if (SM) maximum(sn);
             stash(st, j + 2, j + 1);
+            load(st, j + 3, j + 2);
         } else {
-            stash(st, j + 2, j + 1);
+            if (j < nact) {
+                scores(j, s);
+                mask(j, s);
+                if (SM) {
+                    maximum(s);
+                    exponentials(s);
+                }
+                split_s(s, ph, pm, pl);
+                accumulate(j, ph, pm, pl);
+            }
+            stash(st, j + 1, j + 1);
+            load(st, j + 2, j + 2);
         }
-        load(st, j + 3, j + 2);
         __syncthreads();
     };
     f16x s0 = f16x{}, s1 = f16x{};
@@ -997,18 +987,18 @@ __global__ __launch_bounds__(NW * 64) void k_attn_b3(const SdpaParams p) {
         }
         __syncthreads();
         if (PIPE) {
-            if (nact > 0) {
-                scores(0, s0);
-                mask(0, s0);
-                if (SM) maximum(s0);
-            }
+            scores(0, s0);
+            mask(0, s0);
             __syncthreads();                 // pass 0 stages over K of block 0
         }
         for (int j = 0; j < nblk; j += 2) {
             pass(j, s0, s1);
             if (j + 1 < nblk) pass(j + 1, s1, s0);
         }
-        if (!PIPE) m_out = m;
+        if (PIPE) {
+#pragma unroll
+            for (int n = 0; n < NTO; ++n) o[n] += low[n];
+        }
     }
     if (tid == 0) out_of_range = 0;
     __syncthreads();
@@ -1018,7 +1008,7 @@ __global__ __launch_bounds__(NW * 64) void k_attn_b3(const SdpaParams p) {
         // the workgroup starts again on the fp32 matrix cores, each wave by itself
 #pragma unroll
         for (int n = 0; n < NTO; ++n) o[n] = f16x{};
-        m = m_out = -INFINITY;
+        m = -INFINITY;
         lsum = 0.f;
         for (int j = 0; j < nact; ++j) {
             f16x s;
@@ -1026,7 +1016,6 @@ __global__ __launch_bounds__(NW * 64) void k_attn_b3(const SdpaParams p) {
             mask(j, s);
             if (SM) {
                 maximum(s);
-                m_out = m;
 #pragma unroll
                 for (int n = 0; n < NTO; ++n)
 #pragma unroll
@@ -1046,7 +1035,7 @@ __global__ __launch_bounds__(NW * 64) void k_attn_b3(const SdpaParams p) {
         dst = p.part + ((int64_t)split * rows + head * p.L) * d;
         if (SM && h == 0 && q < p.L) {
             float* stt = p.stat + ((int64_t)split * rows + head * p.L + q) * 2;
-            stt[0] = m_out;
+            stt[0] = m;
             stt[1] = l;
         }
     } else if (SM) {

@@ -373,7 +373,7 @@ enum Route : int32_t {
     R_VALU_DOT2 = 5, R_S24_VALU = 6, R_S24_I8LIMB = 7,
     R_ATTN_F32_MFMA = 8, R_ATTN_I32_MFMA = 9, R_ATTN_I32_VALU = 10,
     R_ATTN_F32_VALU = 11,   // fp32 attention on the vector ALU (shapes the MFMA kernel does not take)
-    R_F32_MFMA = 12, R_F32_VALU = 13,   // FP32 convolution: matrix cores (six bf16 products) / vector ALU
+    R_F32_MFMA = 12, R_F32_VALU = 13,   // FP32 convolution: matrix cores (eight bf16 products) / vector ALU
 };
 
 // Fixed device scratch of the allocation-free GEMM entry point: its size,

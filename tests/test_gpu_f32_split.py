@@ -1,7 +1,8 @@
 """FP32 kernels on the bf16 matrix cores: every float as three bf16 terms.
 
 The elementwise bound is the a-priori one of fp32 sums in any order, u = 2^-24
-per term; the dropped products (below 3 * 2^-26 of each) lie inside it.  Values
+per term; the dropped product (l l, at most 2^-34 of the whole) lies inside it,
+and a sum of one product rounds as an fp32 multiplication does.  Values
 for which the split is not exact, or whose products could overflow, take the
 fp32 matrix cores, so infinities, NaN and tiny values behave as in fp32.
 """
@@ -79,6 +80,54 @@ def test_core_not_finite(L, value):
     Q[7, 3], V[L - 2, 5] = 0.0, 0.0
     bound = core_bound(Q, K, V)
     assert (np.abs(O[ok] - R[ok]) <= bound[ok]).all()
+
+
+# One non-zero product a sum.  Every step is exact but the smaller terms' sum
+# (2^-7 of the product at most, rounded to 2^-24 of itself) and the last
+# addition (half an ulp).  0x1.00ff8p0 = 1 + 2^-8 - 2^-17 has the largest
+# second and third terms.
+HALF_ULP = 0.5 + 2.0 ** -6
+
+
+def ulps(y, r):
+    return np.abs(y - r) / 2.0 ** (np.floor(np.log2(np.abs(r))) - 23)
+
+
+@pytest.mark.parametrize("k,Ci,Co", [(3, 64, 128), (1, 32, 33)])
+def test_conv_one_product(k, Ci, Co):
+    rng = np.random.default_rng(Ci)
+    x = rng.standard_normal((4, Ci, 28, 28)).astype(np.float32)
+    w = np.zeros((Co, Ci, k, k), np.float32)
+    w[np.arange(Co), np.arange(Co) % Ci, k // 2, k // 2] = rng.standard_normal(Co)
+    w[0, 0, k // 2, k // 2] = x[0, 0, 0, 0] = float.fromhex("0x1.00ff8p0")
+    y = host(qx.conv2d_gemm_t(dev(x), dev(w), 1, k // 2))
+    r = conv_ref(x, w, 1, k // 2)
+    assert (r != 0).all() and ulps(y, r).max() <= HALF_ULP
+
+
+@pytest.mark.parametrize("d", [32, 64, 96, 128])
+def test_core_one_product(d):
+    # one key, one coordinate: (q k) v, each product to half an ulp
+    rng = np.random.default_rng(d)
+    for i in range(8):
+        Q, K, V = np.zeros((1, d), np.float32), np.zeros((1, d), np.float32), rng.standard_normal((1, d)).astype(np.float32)
+        Q[0, i], K[0, i] = rng.standard_normal(2) if i else [float.fromhex("0x1.00ff8p0")] * 2
+        O = host(qx.attn_core(dev(Q), dev(K), dev(V)))
+        S = np.float32(Q[0, i]) * np.float64(K[0, i])
+        # S to half an ulp, then S's float times V to half an ulp
+        s = np.array([np.float32(S), np.nextafter(np.float32(S), np.float32(np.inf)),
+                      np.nextafter(np.float32(S), np.float32(-np.inf))], np.float32)
+        s = s[ulps(s.astype(np.float64), S) <= HALF_ULP]
+        err = np.stack([ulps(O, np.float64(t) * V) for t in s]).max(axis=(1, 2))
+        assert err.min() <= HALF_ULP
+
+
+def test_conv_constant_operands():
+    # the dropped terms of equal operands share one sign
+    c = np.float32(float.fromhex("0x1.00ff8p0"))
+    x, w = np.full((1, 32, 9, 9), c), np.full((64, 32, 1, 1), c)
+    y = host(qx.conv2d_gemm_t(dev(x), dev(w)))
+    assert ulps(y, conv_ref(x, w, 1, 0)).max() <= HALF_ULP
 
 
 def sdpa_ref(Q, K, V, scale, causal):
