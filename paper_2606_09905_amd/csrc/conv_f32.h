@@ -6,14 +6,12 @@
 //  1. Prep: x NCHW -> a zero-bordered NHWC image of split values,
 //     xs [N][H+2p][W+2p][Ci/32][3][32] bf16 (a pixel's 32 channels: h, m, l,
 //     192 contiguous bytes), and w OIHW -> ws [Cop][Kd/32][3][32] with
-//     k = (kh*KW + kw)*Ci + ci.  Values the split cannot hold are written as
-//     NaN.
+//     k = (kh*KW + kw)*Ci + ci; both times kSplitScale.
 //  2. Contraction: a K tile is 32 channels of one kernel tap, gathered per
 //     pixel straight from the image into LDS (direct-to-LDS loads, a ring of
-//     stages).  Products of split values are finite, so a NaN among a wave's
-//     sums means such a value, and the wave contracts its tile again on the
-//     fp32 matrix cores from x and w.  Few tiles split K over workgroups; the
-//     partial outputs are added in split order.
+//     stages).  A wave whose sums are not all finite contracts its tile again
+//     on the fp32 matrix cores from x and w.  Few tiles split K over
+//     workgroups; the partial outputs are added in split order.
 //
 // Bound (8x64x56x56 -> 128, 3x3): 392 tiles on 256 CUs, so 17 us of matrix
 // products on the busiest SIMDs; the kernel takes about 31 us of the 38 (46 on
@@ -73,12 +71,10 @@ __global__ __launch_bounds__(256) void k_conv_prep_f32(const ConvF32Params p) {
             for (int e = 0; e < 8; ++e) v[e] = src[e * taps];
         }
     }
-    SplitRange<-100, 60> rg;
 #pragma unroll
-    for (int e = 0; e < 8; ++e) rg.see(v[e]);
+    for (int e = 0; e < 8; ++e) v[e] *= kSplitScale;
     b8 h, m, l;
     split3(v, h, m, l);
-    if (rg.bad()) h = __builtin_bit_cast(b8, u4{0x7FFF7FFFu, 0x7FFF7FFFu, 0x7FFF7FFFu, 0x7FFF7FFFu});
     if (!image) {
         if (co >= p.Cop) return;
         unsigned char* dst = p.ws + (wv / 4 * 3) * 64 + (wv & 3) * 16;   // 32-channel chunk wv / 4
@@ -268,15 +264,15 @@ __global__ __launch_bounds__(BM * BN / WN) void k_conv_f32(const ConvF32Params p
     for (int j = 0; j < TN; ++j) {
         const int gn = n0 + wn * WN + j * 32 + l32;
         const int n_img = min(gn, p.P - 1) / p.hw, n_pix = min(gn, p.P - 1) - n_img * p.hw;
-        bool nan = false;
+        bool redo = false;
 #pragma unroll
         for (int i = 0; i < 2; ++i)
 #pragma unroll
             for (int r = 0; r < 16; ++r) {
-                acc[i][j][r] += low[i][j][r];
-                nan |= acc[i][j][r] != acc[i][j][r];
+                acc[i][j][r] = (acc[i][j][r] + low[i][j][r]) * (1.f / (kSplitScale * kSplitScale));
+                redo |= !(fabsf(acc[i][j][r]) < INFINITY);
             }
-        if (__ballot(nan && gn < p.P) != 0) {
+        if (__ballot(redo) != 0) {
             const int oh = n_pix / g.Wo, ow = n_pix - oh * g.Wo;
             const float* xi = p.x + (int64_t)n_img * g.Ci * g.H * g.W;
             acc[0][j] = f16x{};

@@ -12,10 +12,12 @@
 // each step rounds its running sum, and only theirs is of full size, one
 // rounding for 16 products where the fp32 cores round for every two.
 //
-// The split is exact, and no product overflows, for x = 0 or
-// 2^ELO <= |x| < 2^EHI; SplitRange notes a value outside (infinities and NaN
-// among them), and what depends on it is contracted on the fp32 matrix cores
-// instead, from the caller's arrays.
+// A bf16 has the exponents of a float and keeps subnormals down to 2^-133, as
+// does the matrix core, so the split of x * kSplitScale is exact down to
+// x's last subnormal bit, 2^-149; the sums are scaled back at the end.
+// Infinities, NaN and |x| >= 2^112 leave a NaN among the terms, and sums that
+// overflow are not finite: whoever finds such a sum contracts again on the
+// fp32 matrix cores, from the caller's arrays.
 #pragma once
 
 #include <hip/hip_runtime.h>
@@ -26,6 +28,8 @@ namespace qx {
 typedef __bf16 b8 __attribute__((ext_vector_type(8)));
 typedef __bf16 b2 __attribute__((ext_vector_type(2)));
 typedef float f2 __attribute__((ext_vector_type(2)));
+
+constexpr float kSplitScale = 65536.f;
 
 // eight floats -> their three bf16 terms
 __device__ __forceinline__ void split3(const float (&x)[8], b8& h, b8& m, b8& l) {
@@ -43,19 +47,5 @@ __device__ __forceinline__ void split3(const float (&x)[8], b8& h, b8& m, b8& l)
     m = __builtin_bit_cast(b8, mw);
     l = __builtin_bit_cast(b8, lw);
 }
-
-// Tracks whether every value seen is 0 or has 2^ELO <= |x| < 2^EHI.
-template <int ELO, int EHI>
-struct SplitRange {
-    uint32_t lo = 0xFFFFFFFFu, hi = 0u;
-    __device__ __forceinline__ void see(float x) {
-        const uint32_t u = __float_as_uint(x) << 1;   // sign dropped
-        hi = max(hi, u);
-        lo = min(lo, u - 1u);                         // 0 wraps to the largest
-    }
-    __device__ __forceinline__ bool bad() const {
-        return hi >= (uint32_t)(EHI + 127) << 24 || lo < ((uint32_t)(ELO + 127) << 24) - 1u;
-    }
-};
 
 }  // namespace qx

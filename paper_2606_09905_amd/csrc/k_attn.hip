@@ -666,6 +666,10 @@ __global__ __launch_bounds__(512) void k_attn_i32s(const AttnParams p) {
 // never change lanes.  One barrier per block; a block's loads are in flight
 // for a whole block before it is staged.
 //
+// Scales: the core takes Q, K and V times kSplitScale and S down to S times it;
+// the softmax form takes V and its probabilities times it (scores need no more
+// than their absolute error, a probability down to 2^-126 all of its bits).
+//
 // Bound: the matrix cores; per 32x32 block and wave 2048 matrix cycles against
 // about 1450 of vector ALU (exponentials, splits).  32 causal heads x 4096 x
 // 64: 444 us, d = 128, 16 x 2048: 243 (616 and 302 on v_mfma_f32_32x32x2f32);
@@ -693,10 +697,8 @@ __global__ __launch_bounds__(NW * 64) void k_attn_b3(const SdpaParams p) {
     constexpr int KB = AKB * KP, VB = D * VP;            // bytes of one plane
     constexpr int NI = (8 * D + NTH - 1) / NTH;          // staging items (8 elements) per thread
     constexpr bool PIPE = !SM && D <= 64;
-    // products of the core reach |q k| d |v| L: its values are held closer to 1
-    typedef SplitRange<SM ? -100 : -40, SM ? 60 : 30> Range;
     __shared__ __align__(16) unsigned char lds[2][3 * (KB + VB)];
-    __shared__ int out_of_range;
+    __shared__ int large_k;
 
     const int tid = threadIdx.x, lane = tid & 63, h = lane >> 5, l32 = lane & 31;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), wave64 = wave * 64;
@@ -743,9 +745,9 @@ __global__ __launch_bounds__(NW * 64) void k_attn_b3(const SdpaParams p) {
     const int q = q0 + l32;           // this lane's query
     // Softmax: Q is taken pre-multiplied by c = scale*log2(e), so the scores
     // come out of the MFMAs already in the base-2 exponent domain.
-    const float c = SM ? p.c : 1.f;
+    const float c = SM ? p.c : kSplitScale;
     b8 qh[KS], qm[KS], ql[KS];        // k-slot (h, e) of step t is d-index 16 t + 8 h + e
-    Range rg;                         // of every value this thread splits
+    float qmax = 0.f, kmax = 0.f;     // largest |q c|, |k| this thread has split
     {
 #pragma unroll
         for (int t = 0; t < KS; ++t) {
@@ -754,10 +756,11 @@ __global__ __launch_bounds__(NW * 64) void k_attn_b3(const SdpaParams p) {
 #pragma unroll
             for (int e = 0; e < 8; ++e) {
                 v[e] *= c;
-                rg.see(v[e]);
+                if (SM) qmax = fmaxf(qmax, fabsf(v[e]));
             }
             split3(v, qh[t], qm[t], ql[t]);
         }
+        if (SM) asm volatile("" : "+v"(qmax));   // found here, not from values kept to the end
     }
     f16x o[NTO], low[NTO];            // low: PIPE only
 #pragma unroll
@@ -807,10 +810,15 @@ __global__ __launch_bounds__(NW * 64) void k_attn_b3(const SdpaParams p) {
             const int iw = wave64 + NTH * i, it = iw + lane, iv = it - 4 * D;
             if (NI * NTH != 8 * D && iw >= 8 * D) break;
             const bool is_k = iw < 4 * D;
+            float v[8];
+            const float scale = SM && is_k ? 1.f : kSplitScale;
 #pragma unroll
-            for (int e = 0; e < 8; ++e) rg.see(st[i][e]);
+            for (int e = 0; e < 8; ++e) {
+                v[e] = st[i][e] * scale;
+                if (SM && is_k) kmax = fmaxf(kmax, fabsf(v[e]));
+            }
             b8 a, b, l;
-            split3(st[i], a, b, l);
+            split3(v, a, b, l);
             unsigned char* dst = is_k ? &lds[jk & 1][(it / (D / 8)) * KP + it % (D / 8) * 16]
                                       : &lds[jv & 1][3 * KB + (iv % D) * VP + iv / D * 16];
             const int plane = is_k ? KB : VB;
@@ -846,7 +854,7 @@ __global__ __launch_bounds__(NW * 64) void k_attn_b3(const SdpaParams p) {
             if (q < p.L) ld8(Q, (unsigned)q * d, t + 8 * h, true, qv);
 #pragma unroll
             for (int e = 0; e < 8; ++e)
-                s = __builtin_amdgcn_mfma_f32_32x32x2f32(kv[e], qv[e] * c, s, 0, 0, 0);
+                s = __builtin_amdgcn_mfma_f32_32x32x2f32(kv[e], SM ? qv[e] * c : qv[e], s, 0, 0, 0);
         }
     };
     // Register r holds key kb + 8*(r/4) + 4*h + r%4.  In a block that
@@ -877,11 +885,11 @@ __global__ __launch_bounds__(NW * 64) void k_attn_b3(const SdpaParams p) {
         alpha = __builtin_amdgcn_exp2f(m - m_use);
         m = m_new;
     };
-    auto exponentials = [&](f16x& s) {
+    auto exponentials = [&](f16x& s, float scale) {
         float ps = 0.f;
 #pragma unroll
         for (int r = 0; r < 16; ++r) {
-            s[r] = __builtin_amdgcn_exp2f(s[r] - m_use);
+            s[r] = __builtin_amdgcn_exp2f(s[r] - m_use) * scale;
             ps += s[r];
         }
         lsum = lsum * alpha + ps;
@@ -891,7 +899,7 @@ __global__ __launch_bounds__(NW * 64) void k_attn_b3(const SdpaParams p) {
         for (int t = 0; t < 2; ++t) {
             float pv[8];
 #pragma unroll
-            for (int e = 0; e < 8; ++e) pv[e] = s[8 * t + e];
+            for (int e = 0; e < 8; ++e) pv[e] = SM ? s[8 * t + e] : s[8 * t + e] * (1.f / kSplitScale);
             split3(pv, ph[t], pm[t], pl[t]);
         }
     };
@@ -962,7 +970,7 @@ __global__ __launch_bounds__(NW * 64) void k_attn_b3(const SdpaParams p) {
                 mask(j, s);
                 if (SM) {
                     maximum(s);
-                    exponentials(s);
+                    exponentials(s, kSplitScale);
                 }
                 split_s(s, ph, pm, pl);
                 accumulate(j, ph, pm, pl);
@@ -1000,12 +1008,27 @@ __global__ __launch_bounds__(NW * 64) void k_attn_b3(const SdpaParams p) {
             for (int n = 0; n < NTO; ++n) o[n] += low[n];
         }
     }
-    if (tid == 0) out_of_range = 0;
-    __syncthreads();
-    if (rg.bad()) out_of_range = 1;
-    __syncthreads();
-    if (out_of_range) {
-        // the workgroup starts again on the fp32 matrix cores, each wave by itself
+    // Split values are finite only where the products are (f32_split.h): an
+    // output that is not starts its wave again on the fp32 matrix cores.  A
+    // score too low for fp32 would end as a probability of 0, so the softmax
+    // form also holds |q| and |k| below 2^60.
+    bool redo = SM && !(qmax < 0x1p60f && fabsf(lsum) < INFINITY);
+#pragma unroll
+    for (int n = 0; n < NTO; ++n)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) redo |= !(fabsf(o[n][r]) < INFINITY);
+    redo = __ballot(redo) != 0;
+    if (SM) {
+        if (tid == 0) large_k = 0;
+        __syncthreads();
+        if (!(kmax < 0x1p60f)) large_k = 1;
+        __syncthreads();
+        redo |= large_k != 0;
+    }
+    // what the sums are multiplied by
+    float lscale = SM ? kSplitScale : 1.f, oscale = kSplitScale * kSplitScale;
+    if (redo) {
+        lscale = oscale = 1.f;
 #pragma unroll
         for (int n = 0; n < NTO; ++n) o[n] = f16x{};
         m = -INFINITY;
@@ -1020,7 +1043,7 @@ __global__ __launch_bounds__(NW * 64) void k_attn_b3(const SdpaParams p) {
                 for (int n = 0; n < NTO; ++n)
 #pragma unroll
                     for (int r = 0; r < 16; ++r) o[n][r] *= alpha;
-                exponentials(s);
+                exponentials(s, 1.f);
             }
             accumulate_f32(j, s);
         }
@@ -1028,7 +1051,7 @@ __global__ __launch_bounds__(NW * 64) void k_attn_b3(const SdpaParams p) {
 
     // lane (q, h), register r of tile n: column 32 n + 8*(r/4) + 4*h + r%4
     const float l = SM ? lsum + __shfl_xor(lsum, 32) : 1.f;
-    float f = 1.f;
+    float f = 1.f / oscale;
     float* dst = p.O + hoff;
     if (p.splits > 1) {
         const int64_t rows = (int64_t)p.BH * p.L;
@@ -1036,10 +1059,10 @@ __global__ __launch_bounds__(NW * 64) void k_attn_b3(const SdpaParams p) {
         if (SM && h == 0 && q < p.L) {
             float* stt = p.stat + ((int64_t)split * rows + head * p.L + q) * 2;
             stt[0] = m;
-            stt[1] = l;
+            stt[1] = l * (1.f / lscale);
         }
     } else if (SM) {
-        f = l > 0.f ? 1.f / l : 0.f;
+        f = l > 0.f ? 1.f / l * (lscale / oscale) : 0.f;
     }
     if (q >= p.L) return;
     dst += (int64_t)q * d;

@@ -2,9 +2,10 @@
 
 The elementwise bound is the a-priori one of fp32 sums in any order, u = 2^-24
 per term; the dropped product (l l, at most 2^-34 of the whole) lies inside it,
-and a sum of one product rounds as an fp32 multiplication does.  Values
-for which the split is not exact, or whose products could overflow, take the
-fp32 matrix cores, so infinities, NaN and tiny values behave as in fp32.
+and a sum of one product rounds as an fp32 multiplication does.  The split of a
+scaled value is exact down to the last subnormal bit of a float, so small values
+take no other path than ordinary ones; where a sum is not finite (infinities,
+NaN, overflow of the scaled sums) the fp32 matrix cores give it again.
 """
 import numpy as np
 import pytest
@@ -51,13 +52,20 @@ def test_core(L, d):
 
 
 @pytest.mark.parametrize("L", [96, 4352])
-@pytest.mark.parametrize("scales", [(2.0 ** 40, 2.0 ** -40, 1.0), (1.0, 1.0, 1e-36), (2.0 ** -70, 2.0 ** 60, 1e10)])
+# exact at every size a float can have: subnormal operands, terms and products,
+# and sums that the scales take to 2^96 and beyond
+@pytest.mark.parametrize("scales", [(2.0 ** 40, 2.0 ** -40, 1.0), (1.0, 1.0, 1e-36), (2.0 ** -70, 2.0 ** 60, 1e10),
+                                    (2.0 ** -39,) * 3, (2.0 ** 28,) * 3, (1e-13, 1e-13, 1.0), (2.0 ** -60, 2.0 ** -60, 1.0),
+                                    (1e-41, 1e20, 1e20), (2.0 ** -72, 2.0 ** -72, 2.0 ** 90), (1e18, 1e-40, 1e18),
+                                    (2.0 ** 31, 2.0 ** 31, 2.0 ** 31), (2.0 ** 45, 2.0 ** 45, 1e-30)])
 def test_core_ranges(L, scales):
     rng = np.random.default_rng(L)
     Q, K, V = ((rng.standard_normal((L, 64)) * s).astype(np.float32) for s in scales)
     O = host(qx.attn_core(dev(Q), dev(K), dev(V)))
-    # results below the smallest normal number lose up to its half ulp per term
-    assert (np.abs(O - orc.attn_f64(Q, K, V)) <= core_bound(Q, K, V) + L * 2.0 ** -149).all()
+    # results below the smallest normal number lose up to its half ulp per term,
+    # and so do scores, each of which is multiplied by a value
+    floor = L * 2.0 ** -149 + 64 * 2.0 ** -149 * np.abs(V).astype(np.float64).sum(axis=0)
+    assert (np.abs(O - orc.attn_f64(Q, K, V)) <= core_bound(Q, K, V) + floor).all()
 
 
 @pytest.mark.parametrize("L", [70, 4352])
@@ -150,14 +158,33 @@ def test_softmax(BH, L, d, causal):
     assert np.linalg.norm(O - R) <= 4e-6 * np.linalg.norm(R)
 
 
+@pytest.mark.parametrize("L", [64, 2000])
+def test_softmax_small_probabilities(L):
+    # Probabilities of 2^-115 beside a maximum whose value is 0.  scale ln 2
+    # makes the base-2 scores the keys' numbers, which are eighths: exact, so a
+    # probability is off by its exponential's error alone (about an ulp).
+    rng = np.random.default_rng(L)
+    Q, K, V = np.zeros((1, L, 32), np.float32), np.zeros((1, L, 32), np.float32), rng.standard_normal((1, L, 32))
+    V = (V * 1e30).astype(np.float32)
+    Q[..., 0] = 1.0
+    K[0, 1:, 0] = -112 - rng.integers(0, 96, L - 1) / 8
+    V[0, 0] = 0.0
+    scale = float(np.float32(np.log(2.0)))
+    assert np.float32(scale * 1.4426950408889634) == 1.0
+    O = host(qx.sdpa_f32(dev(Q), dev(K), dev(V), scale, False))
+    P = 2.0 ** K[0, :, 0].astype(np.float64)
+    R, A = P @ V[0].astype(np.float64), P @ np.abs(V[0]).astype(np.float64)
+    assert (np.abs(O[0] - R) <= (8 + L / 32 + 8) * U * A).all()
+
+
 @pytest.mark.parametrize("BH,L", [(2, 100), (20, 512)])
 def test_softmax_ranges(BH, L):
     d = 64
     rng = np.random.default_rng(L)
     Q, K, V = (rng.standard_normal((BH, L, d)).astype(np.float32) for _ in range(3))
     V0 = V.copy()
-    V[0] *= 1e-37                       # below the split's exact range
-    V[1] *= 1e30                        # and above it
+    V[0] *= 1e-37
+    V[1] *= 1e30                        # some sums overflow at the split's scale
     K[1, 3, 5] = 1e-33
     K[0, L - 1, 0] = np.inf             # an infinite score of either sign
     O = host(qx.sdpa_f32(dev(Q), dev(K), dev(V), 0.125, True))
@@ -195,6 +222,52 @@ def test_conv(case):
     bound = (Ci * k * k + 4) * U * conv_ref(np.abs(x), np.abs(w), stride, pad)
     assert (np.abs(y - conv_ref(x, w, stride, pad)) <= bound).all()
     assert np.array_equal(y, host(qx.conv2d_gemm_t(dev(x), dev(w), stride, pad)))
+
+
+@pytest.mark.parametrize("case", [CONV[2], CONV[3], CONV[6]])
+@pytest.mark.parametrize("scales", [(2.0 ** -61, 2.0 ** -61), (2.0 ** -99, 2.0 ** -20), (2.0 ** 40, 2.0 ** 40),
+                                    (2.0 ** 57, 2.0 ** 57), (1e-41, 1e10), (1e25, 1e-44), (2.0 ** -75, 2.0 ** -75)])
+def test_conv_ranges(case, scales):
+    N, Ci, H, W, Co, k, stride, pad = case
+    rng = np.random.default_rng(sum(case))
+    x = (rng.standard_normal((N, Ci, H, W)) * scales[0]).astype(np.float32)
+    w = (rng.standard_normal((Co, Ci, k, k)) * scales[1]).astype(np.float32)
+    y = host(qx.conv2d_gemm_t(dev(x), dev(w), stride, pad))
+    R, A = conv_ref(x, w, stride, pad), conv_ref(np.abs(x), np.abs(w), stride, pad)
+    assert (np.abs(y.astype(np.float64) - R) <= Ci * k * k * (U * A + 2.0 ** -149) + 4 * U * A).all()
+
+
+def best_time(ex, inputs):
+    out = torch.empty(ex.out_shape, dtype=ex.out_dtype, device="cuda")
+    times = []
+    for _ in range(6):
+        a, b = (torch.cuda.Event(enable_timing=True) for _ in range(2))
+        a.record()
+        for _ in range(10):
+            ex.run(inputs, out)
+        b.record()
+        torch.cuda.synchronize()
+        times.append(a.elapsed_time(b))
+    return min(times)
+
+
+def test_small_values_take_the_same_path():
+    # the fp32 matrix cores' path costs three to five times as much
+    g = torch.Generator(device="cuda").manual_seed(5)
+    Q, K, V = (torch.randn((16, 2048, 64), generator=g, device="cuda") for _ in range(3))
+    with qx.Executor.sdpa_f32(16, 2048, 64, 0.125, True) as ex:
+        t = best_time(ex, [Q, K, V])
+        K2, V2 = K.clone(), V.clone()
+        K2[:, 5, 3], V2[:, 7, 1] = 1e-33, 1e-40
+        assert best_time(ex, [Q, K2, V2]) < 2 * t
+    with qx.Executor.attn("f32", 4096, 64, 0) as ex:
+        q, k, v = (t.reshape(-1, 64)[:4096].contiguous() for t in (Q, K, V))
+        assert best_time(ex, [q * 1e-13, k * 1e-13, v * 1e-13]) < 2 * best_time(ex, [q, k, v])
+    x, w = torch.randn((8, 64, 56, 56), generator=g, device="cuda"), torch.randn((128, 64, 3, 3), generator=g, device="cuda")
+    with qx.Executor.conv2d_t("f32", 8, 64, 56, 56, 128, 3, 3, 1, 1) as ex:
+        t = best_time(ex, [x, w])
+        w[5::64, 1, 0, 0] = 1e-40
+        assert best_time(ex, [x, w]) < 2 * t
 
 
 @pytest.mark.parametrize("case", [CONV[2], CONV[3], CONV[5]])
