@@ -258,12 +258,12 @@ __global__ __launch_bounds__(BM * BN / WN) void k_conv_f32(const ConvF32Params p
 #pragma unroll
     for (int e = 0; e < TERMS; ++e) term(f1, PA[e], PB[e]);
 
-    const int taps = g.KH * g.KW;
+    const int taps = g.KH * g.KW, img_px = g.H * g.W;
     float* out = p.part ? p.part + (int64_t)blockIdx.y * p.part_stride : p.y;
 #pragma unroll
     for (int j = 0; j < TN; ++j) {
-        const int gn = n0 + wn * WN + j * 32 + l32;
-        const int n_img = min(gn, p.P - 1) / p.hw, n_pix = min(gn, p.P - 1) - n_img * p.hw;
+        const int gn = n0 + wn * WN + j * 32 + l32, pix = min(gn, p.P - 1);
+        const int n_img = pix / p.hw, n_pix = pix - n_img * p.hw;
         bool redo = false;
 #pragma unroll
         for (int i = 0; i < 2; ++i)
@@ -274,29 +274,42 @@ __global__ __launch_bounds__(BM * BN / WN) void k_conv_f32(const ConvF32Params p
             }
         if (__ballot(redo) != 0) {
             const int oh = n_pix / g.Wo, ow = n_pix - oh * g.Wo;
-            const float* xi = p.x + (int64_t)n_img * g.Ci * g.H * g.W;
-            acc[0][j] = f16x{};
-            acc[1][j] = f16x{};
-            // 16 k at a time, their loads in flight together
-            for (int k0 = tile0 * 32; k0 < (tile0 + ktiles) * 32; k0 += 16) {
-                float bv[8], av[2][8];
+            const float* xi = p.x + ((int64_t)n_img * g.Ci + hh) * img_px;
+            const float* wi[2];
 #pragma unroll
-                for (int e = 0; e < 8; ++e) {
-                    const int k = k0 + 2 * e + hh, tap = k / g.Ci, ci = k - tap * g.Ci, kh = tap / g.KW, kw = tap - kh * g.KW;
-                    const int ih = oh * g.stride + kh - g.pad, iw = ow * g.stride + kw - g.pad;
-                    const bool in = ih >= 0 && ih < g.H && iw >= 0 && iw < g.W;
-                    bv[e] = in ? xi[((int64_t)ci * g.H + ih) * g.W + iw] : 0.f;
+            for (int i = 0; i < 2; ++i) {
+                wi[i] = p.w + ((int64_t)min(m0 + wm * 64 + i * 32 + l32, p.Co - 1) * g.Ci + hh) * taps;
+                acc[i][j] = f16x{};
+            }
+            const int chunks = g.Ci / 32;
+            int tap = tile0 / chunks, ci = (tile0 - tap * chunks) * 32, kh = tap / g.KW, kw = tap - kh * g.KW;
+            // A K tile at a time, its loads in flight together.  8x64x56x56 ->
+            // 128 with every wave here 165 us, with one of them 92 (183 and
+            // 111 with half a tile and divisions for every element).
+            for (int t = 0; t < ktiles; ++t) {
+                const int ih = oh * g.stride + kh - g.pad, iw = ow * g.stride + kw - g.pad;
+                const bool in = ih >= 0 && ih < g.H && iw >= 0 && iw < g.W;
+                const float* xs = xi + (int64_t)ci * img_px + (in ? ih * g.W + iw : 0);
+                float bv[16], av[2][16];
 #pragma unroll
-                    for (int i = 0; i < 2; ++i) {
-                        const int gm = m0 + wm * 64 + i * 32 + l32;
-                        av[i][e] = gm < p.Co ? p.w[((int64_t)gm * g.Ci + ci) * taps + tap] : 0.f;
-                    }
+                for (int e = 0; e < 16; ++e) {
+                    bv[e] = xs[(unsigned)(2 * e) * (unsigned)img_px];
+#pragma unroll
+                    for (int i = 0; i < 2; ++i) av[i][e] = wi[i][((int64_t)ci + 2 * e) * taps + tap];
                 }
 #pragma unroll
-                for (int e = 0; e < 8; ++e)
+                for (int e = 0; e < 16; ++e)
 #pragma unroll
                     for (int i = 0; i < 2; ++i)
-                        acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(av[i][e], bv[e], acc[i][j], 0, 0, 0);
+                        acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(av[i][e], in ? bv[e] : 0.f, acc[i][j], 0, 0, 0);
+                if ((ci += 32) == g.Ci) {
+                    ci = 0;
+                    ++tap;
+                    if (++kw == g.KW) {
+                        kw = 0;
+                        ++kh;
+                    }
+                }
             }
         }
         if (gn >= p.P) continue;

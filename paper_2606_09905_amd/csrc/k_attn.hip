@@ -844,14 +844,18 @@ __global__ __launch_bounds__(NW * 64) void k_attn_b3(const SdpaParams p) {
         s += slow;
         if (!PIPE) __builtin_amdgcn_sched_barrier(0);
     };
+    // the same from the caller's arrays, on the fp32 matrix cores
     auto scores_f32 = [&](int j, f16x& s) {
         const int key = key_lo + j * AKB + l32;
+        const unsigned kr = (unsigned)min(key, key_hi - 1) * d;
+        unsigned qr = (unsigned)min(q, p.L - 1) * d;
+        asm volatile("" : "+v"(qr));      // read again: Q's values are not kept from the start for this
         s = f16x{};
-#pragma unroll 1
+#pragma unroll 2
         for (int t = 0; t < D; t += 16) {
-            float kv[8] = {}, qv[8] = {};
-            if (key < key_hi) ld8(Kp, (unsigned)key * d, t + 8 * h, true, kv);
-            if (q < p.L) ld8(Q, (unsigned)q * d, t + 8 * h, true, qv);
+            float kv[8], qv[8];
+            ld8(Kp, kr, t + 8 * h, true, kv);
+            ld8(Q, qr, t + 8 * h, true, qv);
 #pragma unroll
             for (int e = 0; e < 8; ++e)
                 s = __builtin_amdgcn_mfma_f32_32x32x2f32(kv[e], SM ? qv[e] * c : qv[e], s, 0, 0, 0);
@@ -934,15 +938,19 @@ __global__ __launch_bounds__(NW * 64) void k_attn_b3(const SdpaParams p) {
         }
     };
     auto accumulate_f32 = [&](int j, const f16x& s) {
+        const int kb = key_lo + j * AKB + 4 * h;
 #pragma unroll
-        for (int r = 0; r < 16; ++r) {
-            const int key = key_lo + j * AKB + 8 * (r >> 2) + 4 * h + (r & 3);
+        for (int n = 0; n < NTO; ++n) {
+            const unsigned col = RAG ? min(n * 32 + l32, d - 1) : n * 32 + l32;
+            float v[16];
 #pragma unroll
-            for (int n = 0; n < NTO; ++n) {
-                const int col = n * 32 + l32;
-                const float v = key < key_hi && (!RAG || col < d) ? Vp[(int64_t)key * d + col] : 0.f;
-                o[n] = __builtin_amdgcn_mfma_f32_32x32x2f32(v, s[r], o[n], 0, 0, 0);
+            for (int r = 0; r < 16; ++r) {
+                const int key = kb + 8 * (r >> 2) + (r & 3);
+                v[r] = Vp[(unsigned)min(key, key_hi - 1) * d + col];
+                if (key >= key_hi) v[r] = 0.f;
             }
+#pragma unroll
+            for (int r = 0; r < 16; ++r) o[n] = __builtin_amdgcn_mfma_f32_32x32x2f32(v[r], s[r], o[n], 0, 0, 0);
         }
     };
 
@@ -1009,8 +1017,10 @@ __global__ __launch_bounds__(NW * 64) void k_attn_b3(const SdpaParams p) {
         }
     }
     // Split values are finite only where the products are (f32_split.h): an
-    // output that is not starts its wave again on the fp32 matrix cores.  A
-    // score too low for fp32 would end as a probability of 0, so the softmax
+    // output that is not starts its wave again on the fp32 matrix cores (where
+    // every wave does, 32 causal heads x 4096 x 64 take 1330 us and the core at
+    // L = 4096, d = 64 101; 1880 and 129 with each load waited for by itself).
+    // A score too low for fp32 would end as a probability of 0, so the softmax
     // form also holds |q| and |k| below 2^60.
     bool redo = SM && !(qmax < 0x1p60f && fabsf(lsum) < INFINITY);
 #pragma unroll
