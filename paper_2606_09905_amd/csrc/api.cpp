@@ -223,6 +223,11 @@ static bool skinny_s24(const GemmSpec& s) {
     return s.s24 && s.N <= 128 && s.ldb <= 128 && s.M * s.batch >= 1024 && s.K <= 4096;
 }
 
+// K slices add into the output, cleared first, so it must be one dense block.
+static bool dense_out(const GemmSpec& s) {
+    return s.out_mode == OUT_CONV || (s.ldc == s.N && (s.batch == 1 || s.sC == s.M * s.N));
+}
+
 // Appends the launches of one integer GEMM; ws_used is the workspace end.
 qx_status plan_int_gemm(const GemmSpec& s, Plan* pl, uint64_t* ws_used) {
     int32_t route = s.route;
@@ -233,11 +238,20 @@ qx_status plan_int_gemm(const GemmSpec& s, Plan* pl, uint64_t* ws_used) {
             // step, four times the step's own cycles, and has no encoded
             // path: large problems take three int8 products instead (bounds
             // 1024, 3x(2435x528x4671) 672 / 224 us, 1000x777x500 22.1 / 15.3;
-            // below the line 512^3 10.8 / 12.2, 2048x2048x128 13.0 / 14.3).
+            // below the line 512^3 10.8 / 12.2, 2048x2048x128 13.0 / 14.3),
+            // but not where the fp16 kernel slices K and the operands are too
+            // much to encode for their use: few tiles (33x33x250000 58 / 386,
+            // 54x362x14648 24 / 34, 256x256x8192 21 / 27; above 16 tiles
+            // 68x743x8110 36 / 30) or one short side (64x8192x8192 112 / 138,
+            // 48x6000x1000 17 / 21; 102x1960x2522 32 / 24).
             if (route == R_F16_EXACT && f16_chunk(s.ba, s.bb) < 64 && feasible_i16(R_I8_KARATSUBA, s.ba, s.bb) &&
                 s.allow_nt && s.K >= 256 && use_i8nt(R_I8_KARATSUBA, s.M, s.N, s.K, s.batch) &&
-                (double)s.M * (double)s.N * (double)s.K * (double)s.batch >= (double)(1 << 28))
-                route = R_I8_KARATSUBA;
+                (double)s.M * (double)s.N * (double)s.K * (double)s.batch >= (double)(1 << 28)) {
+                const int64_t Mp = pad_up(s.M, 64), Np = pad_up(s.N, 64), tiles = Mp / 64 * (Np / 64) * s.batch;
+                const bool sliced = dense_out(s) && reg_staged_ksplit(R_F16_EXACT, s.M, s.N, s.K, s.batch) > 1;
+                const bool short_side = s.batch == 1 && tiles >= 64 && Mp * Np <= 100 * (s.M + s.N);
+                if (!sliced || (tiles > 16 && !short_side)) route = R_I8_KARATSUBA;
+            }
         }
         if (!route_applies_i16(route))
             return fail(QX_ERR_INVALID_ARG, "route %d does not apply to an int16 contraction", route);
@@ -286,9 +300,7 @@ qx_status plan_int_gemm(const GemmSpec& s, Plan* pl, uint64_t* ws_used) {
         int32_t ksplit = 1;
         if (!skinny) {
             const int64_t tiles = ((s.M + 63) / 64) * ((s.N + 63) / 64) * s.batch;
-            const bool dense_out = s.out_mode == OUT_CONV ||
-                                   (s.ldc == s.N && (s.batch == 1 || s.sC == s.M * s.N));
-            if (dense_out && tiles > 0 && tiles < 1024 && s.K >= 256) {
+            if (dense_out(s) && tiles > 0 && tiles < 1024 && s.K >= 256) {
                 const int64_t want = std::min<int64_t>({(1024 + tiles - 1) / tiles, s.K / 128, 8});
                 if (want > 1 && s.batch * want <= 65535) ksplit = (int32_t)want;
             }
@@ -550,10 +562,7 @@ qx_status plan_int_gemm(const GemmSpec& s, Plan* pl, uint64_t* ws_used) {
         g.chunk_tiles = chunk >= 64 ? (int32_t)(chunk / 64) : 0;
         info.chunk = chunk >= 64 ? (int32_t)(chunk / 64 * 64) : 16;
     }
-    // K slices add into the output, cleared first, so it must be one dense block
-    const bool dense_out = s.out_mode == OUT_CONV ||
-                           (s.ldc == s.N && (s.batch == 1 || s.sC == s.M * s.N));
-    g.ksplit = dense_out ? reg_staged_ksplit(route, s.M, s.N, s.K, s.batch) : 1;
+    g.ksplit = dense_out(s) ? reg_staged_ksplit(route, s.M, s.N, s.K, s.batch) : 1;
     info.k_splits = g.ksplit > 1 ? g.ksplit : 0;
     if (g.ksplit > 1) add_fill_out(pl, s.M * s.N * s.batch);
     LaunchRec rec;

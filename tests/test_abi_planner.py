@@ -183,6 +183,21 @@ def test_route_boundaries(b, route):
     assert qx.plan_gemm_i16i32(64, 64, 64, 1, b, b)["route_name"] == route
 
 
+# Bounds whose fp16 chunk is under one K tile: int8 planes when large, but not
+# where the fp16 kernel slices K over few tiles or a side is too short for the
+# other operand's encoding to pay.
+@pytest.mark.parametrize("batch,M,N,K,route", [
+    (1, 33, 33, 250000, "f16_exact"), (1, 64, 8192, 8192, "f16_exact"), (1, 6000, 40, 1200, "f16_exact"),
+    (8, 64, 64, 8192, "f16_exact"), (1, 256, 256, 8192, "f16_exact"), (1, 320, 256, 8192, "i8_karatsuba"),
+    (1, 128, 8192, 8192, "i8_karatsuba"), (1, 102, 1960, 2522, "i8_karatsuba"), (1, 1000, 777, 500, "i8_karatsuba"),
+    (1, 512, 512, 512, "f16_exact"), (3, 2435, 528, 4671, "i8_karatsuba"), (1, 2911, 63, 5291, "i8_karatsuba"),
+])
+def test_flushing_chunk_routes(batch, M, N, K, route):
+    p = qx.plan_gemm_i16i32(M, N, K, batch, 1024, 1024)
+    assert p["route_name"] == route
+    assert (p["workspace_bytes"] == 0) == (route == "f16_exact")
+
+
 @pytest.mark.parametrize("ba,bb,chunk", [
     (128, 128, 1024), (256, 256, 256), (255, 255, 256), (300, 300, 176), (512, 512, 64),
     (724, 724, 32), (1024, 1024, 16), (2048, 512, 16), (1, 2048, 8192),

@@ -96,6 +96,15 @@ def test_conv_i32_few_channels(N, Ci, H, W, Co, k, stride):
     assert np.array_equal(auto.cpu().numpy(), orc.conv2d_s24(x, w, stride, k // 2))
 
 
+@pytest.mark.parametrize("batch,M,N,K", [(1, 33, 33, 250001), (1, 64, 4161, 1025), (8, 61, 64, 8193), (1, 250, 256, 4300)])
+def test_flushing_bounds_sliced(batch, M, N, K):
+    assert qx.plan_gemm_i16i32(M, N, K, batch, 1024, 1024)["route_name"] == "f16_exact"
+    rng = np.random.default_rng(K)
+    A, B = ints(rng, (batch, M, K), -1024, 1024, np.int16), ints(rng, (batch, K, N), -1024, 1024, np.int16)
+    C = run(qx.Executor.gemm_i16i32(M, N, K, batch, 1024, 1024), A, B)
+    assert np.array_equal(C, orc.gemm_i16i32(A, B))
+
+
 @pytest.mark.parametrize("M,N,K", [(1024, 1024, 257), (700, 801, 500)])
 def test_flushing_bounds_large(M, N, K):
     # bounds whose chunk is under one K tile: three int8 products when large
