@@ -930,14 +930,22 @@ qx_status plan_conv_t(Plan* pl, int32_t dt, int64_t N, int64_t Ci, int64_t H, in
     // ones: explicit lowering col [Kd][P] int32, then the smul24 GEMM.
     if (route < 0 || route > R_F32_VALU) return fail(QX_ERR_INVALID_ARG, "unknown route %d", route);
     const bool gather = (route == R_AUTO || route == R_S24_I8LIMB) && use_i8nt(R_S24_I8LIMB, Co, P, Kd, 1);
-    // few output channels: a direct vector-ALU kernel (a GEMM tile would be
-    // mostly empty)
-    // (a thread walks all of C_in*KH*KW, so long sums want pixels enough to
-    // hide it: 13x256x25x24 -> 16 1x1 429 us against 33 through the limbs,
-    // 2x16x28x28 3x3 53 / 20, 32x32x56x56 3x3 146 / 155, 8x1x32x32 -> 6 5x5
-    // 10.0 / 11.5)
+    // Few output channels: a direct vector-ALU kernel (a GEMM tile would be
+    // mostly empty).  A thread walks all of C_in*KH*KW for each of its pixels,
+    // waiting on the loads: about 0.1 us a step where the kernel's width is a
+    // compiled one (3, 5), 0.05 for each of eight words a kernel row
+    // otherwise.  The limbs start about 9 us later and take 5 ps for every
+    // element of the column matrix.  Direct / limbs, us: 64x6x30x30 -> 16 3x3
+    // 17.8 / 33.5, 60x3x32x32 -> 6 5x5 24 / 40, 12x2x67x67 -> 10 5x5 10.6 /
+    // 33; 13x256x25x24 -> 16 1x1 429 / 33, 2x16x28x28 3x3 53 / 20,
+    // 4x100x120x120 3x3 469 / 261.  From 65536 pixels on and for short sums it
+    // stays direct.
+    const double direct_us = (KW == 3 || KW == 5 ? 0.1 : 0.05 * 8 / (double)std::max<int64_t>(KW, 1)) *
+                             conv_direct_pixels((int)Wo) * (double)Kd;
+    const double limbs_us = 9 + 5e-6 * (double)P * (double)Kd;
     const bool direct = Co <= 16 && Kd <= 1024 && KW <= 8 &&
-                        (route == R_S24_VALU || (route == R_AUTO && !gather && (Kd <= 48 || P >= (1 << 16))));
+                        (route == R_S24_VALU ||
+                         (route == R_AUTO && !gather && (Kd <= 48 || P >= (1 << 16) || direct_us < limbs_us)));
     if (direct) {
         info.route = R_S24_VALU;
         info.products = 1;

@@ -416,10 +416,12 @@ void build_conv_pool(int layer, const ConvPoolParams& p0, LaunchRec* rec) {
     rec->set_params(p);
 }
 
+int conv_direct_pixels(int wo) { return wo % 4 == 0 ? 4 : wo % 2 == 0 ? 2 : 1; }
+
 void build_conv_direct_s24(const ConvDirectParams& p0, LaunchRec* rec) {
     ConvDirectParams p = p0;
     const int kw = p.g.KW, wo = p.g.Wo;
-    const int pxt = wo % 4 == 0 ? 4 : wo % 2 == 0 ? 2 : 1;
+    const int pxt = conv_direct_pixels(wo);
     const int dco = p.Co <= 8 ? 8 : 16;
     const int64_t hw = (int64_t)p.g.Ho * wo;
     const int64_t chw = (int64_t)p.g.Ci * p.g.H * p.g.W;

@@ -415,6 +415,7 @@ void build_minmax(const MinMaxParams& p, LaunchRec* partial, LaunchRec* final_re
 void build_pool2(int32_t kind, const PoolParams& p, LaunchRec* rec);
 void build_relu(const ReluParams& p, LaunchRec* rec);
 void build_conv_pool(int layer, const ConvPoolParams& p, LaunchRec* rec);
+int conv_direct_pixels(int wo);   // pixels of a row of wo that a thread of the direct kernel makes
 void build_conv_direct_s24(const ConvDirectParams& p, LaunchRec* rec);
 // fp16-exact route for large problems: encoders + direct-to-LDS NT GEMM.
 void nt_tile_shape(int64_t M, int64_t N, int64_t batch, int* bm, int* bn);

@@ -103,6 +103,19 @@ def test_limb_routes_take_the_encode_nt_structure_when_large():
     assert qx.plan_gemm_i16i32(64, 64, 64, 1, 127, 127)["kernels"] == 1
 
 
+# INT32 convolutions of at most 16 channels: direct (one launch, no workspace)
+# while the walk over the sum is short for its pixels, else through the limbs
+@pytest.mark.parametrize("N,Ci,H,Co,k,stride,direct", [
+    (64, 6, 30, 16, 3, 1, True), (60, 3, 32, 6, 5, 1, True), (12, 2, 67, 10, 5, 1, True), (9, 16, 69, 16, 3, 1, True),
+    (3, 6, 14, 8, 3, 2, True), (2, 16, 28, 16, 3, 1, False), (13, 256, 25, 16, 1, 1, False), (8, 49, 16, 16, 1, 1, False),
+    (4, 100, 120, 16, 3, 1, False), (16, 32, 56, 16, 3, 1, False), (8, 1, 32, 6, 5, 1, True), (32, 32, 56, 16, 3, 1, True),
+])
+def test_conv_i32_few_channel_routes(N, Ci, H, Co, k, stride, direct):
+    p = qx.plan_conv2d_t("i32", N, Ci, H, H, Co, k, k, stride, k // 2)
+    assert p["route_name"] == ("s24_valu" if direct else "s24_i8limb")
+    assert (p["workspace_bytes"] == 0) == direct
+
+
 def test_conv_f32_i32_plans():
     # FP32: the fp32 matrix cores when C_in % 32 == 0 (prep launch + gathering
     # NT GEMM), else explicit lowering + vector-ALU fp32 GEMM
