@@ -212,8 +212,8 @@ qx_status qgemm_i16i32_noalloc(const int16_t* A, const int16_t* B, int32_t* C,
  * tensor is BH = B*H heads).  causal = 1 lets query i see keys j <= i only;
  * causal = 0 sees all L keys.  scale: any finite value (1/sqrt(d) is the
  * usual one).  The softmax is taken online over 32-key blocks with a
- * running maximum; key splits (used when BH * ceil(L/128) < 512) are merged
- * in a fixed order, so repeated runs are bit-identical.
+ * running maximum; where that is faster the keys are split over workgroups
+ * and the parts merged in a fixed order, so repeated runs are bit-identical.
  * BH in [0, 65535], L in [0, 2^20], d in [0, 128]; BH*L*d <= 2^34; any 0
  * size is a no-op.  Q, K, V 16-byte aligned when d % 32 == 0, 4-byte
  * otherwise.  Returns QX_ERR_INVALID_ARG for a non-finite scale or

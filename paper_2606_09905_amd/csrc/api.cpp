@@ -1208,16 +1208,66 @@ static int attn_stream_qt(int64_t L) {
     return 2;
 }
 
-// Key splits of the FP32 attention kernels, on 32-key blocks: enough for
-// `target` groups of four waves over `groups` of them per split, but at least
-// four key blocks each (a split of fewer costs more in the launch that joins
-// the splits: 128 heads of 128 14.6 us with one split, 21.5 with two; one
-// head of 64 10.2 against 12.3).
-void attn_f32_splits(int64_t L, int64_t groups, int64_t target, int64_t* splits, int64_t* kps) {
+// Queries per workgroup (128: four waves, 256: eight) and key splits (whole
+// 32-key blocks) of the FP32 attention kernels: the least of an estimated time.
+// A workgroup takes a set-up and a time for every block of its keys; a CU holds
+// one workgroup of eight waves, two of four where d <= 64, and what the busiest
+// one takes counts; splits add a launch and a pass over their outputs.  The
+// times (us) are fitted to 1365 measured ones of 79 shapes (one to 128 heads, L
+// 64 to 8192, all d, both sizes, 1 to 32 splits), off by 5% on average.  More
+// splits are taken for a gain of 2%, 256 queries for one of 5% (they want twice
+// the splits, and so twice the workspace); the choice is within 1.3% of a
+// shape's fastest on average, 17% at most.  Filling the chip with at least four
+// blocks a split, the size chosen by BH L d > 2^18, left the core at 208 x 96 at
+// 18.4 us (now 10.9; the fp32 matrix cores 10.0), 2 heads of 7878 x 64 at 298
+// (206), L = 3693, d = 128 at 90 (65).
+struct AttnF32Shape {
+    int queries;
+    int64_t splits, kps;
+};
+AttnF32Shape attn_f32_shape(bool softmax, int64_t BH, int64_t L, int64_t d, bool causal) {
+    struct Times {
+        double setup, join, per_out;             // a workgroup, a second launch, an output of a split
+        double one[4], two[2], eight[4];         // a block, by (d + 31) / 32: a workgroup of four waves, two
+    };                                           // of them on a CU, one of eight
+    static const Times core = {0.65, 3.4, 2.4e-6, {0.84, 1.61, 2.74, 3.74}, {1.41, 2.67}, {1.23, 2.45, 3.5, 5.2}};
+    static const Times sm = {0.8, 5.0, 3.2e-6, {1.18, 2.07, 3.3, 4.17}, {1.41, 2.96}, {1.56, 2.67, 4.2, 5.15}};
+    const Times& t = softmax ? sm : core;
     const int64_t kblocks = (L + 31) / 32;
-    const int64_t n = std::min<int64_t>((target + groups - 1) / groups, (kblocks + 3) / 4);
-    *kps = (kblocks + n - 1) / n * 32;
-    *splits = (L + *kps - 1) / *kps;
+    const int dt = (int)((d + 31) / 32) - 1;
+    AttnF32Shape best{};
+    double best_us = 0;
+    for (int q : {128, 256}) {
+        const int64_t held = q == 128 && dt < 2 ? 2 : 1;
+        AttnF32Shape mine{};
+        double mine_us = 0;
+        for (int64_t n = 1; n <= std::min<int64_t>(kblocks, 64); ++n) {
+            const int64_t per = (kblocks + n - 1) / n;
+            if ((kblocks + per - 1) / per != n) continue;
+            auto rounds = [&](int64_t k) {   // k workgroups on one CU
+                if (q == 256) return (double)k * (t.eight[dt] * (double)per + t.setup);
+                const double one = t.one[dt] * (double)per + t.setup;
+                if (held == 1) return (double)k * one;
+                return (double)(k / 2) * (t.two[dt] * (double)per + t.setup) + (double)(k % 2) * one;
+            };
+            const int64_t wgs = (L + q - 1) / q * BH * n, k = (wgs + 255) / 256;
+            double us = rounds(k);
+            if (causal && k > held)          // the triangle's share, the longest workgroups first
+                us = std::max(rounds(1), (0.5 + 0.5 * std::min(1.0, (double)q / (double)L)) * (double)wgs / 256 *
+                                             rounds(held) / (double)held);
+            us += 3;                         // a launch
+            if (n > 1) us += t.join + t.per_out * (double)n * (double)BH * (double)L * (double)d;
+            if (n == 1 || us < 0.98 * mine_us) {
+                mine_us = us;
+                mine = {q, n, per * 32};
+            }
+        }
+        if (q == 128 || mine_us < 0.95 * best_us) {
+            best_us = mine_us;
+            best = mine;
+        }
+    }
+    return best;
 }
 
 qx_status plan_attn(Plan* pl, int32_t dt, int64_t L, int64_t d, int32_t bound, int32_t route) {
@@ -1317,16 +1367,17 @@ qx_status plan_attn(Plan* pl, int32_t dt, int64_t L, int64_t d, int32_t bound, i
         a.L = (int32_t)L; a.d = (int32_t)d; a.splits = (int32_t)splits; a.keys_per_split = (int32_t)kps;
         a.limbs = 3;
         a.qt = qt;
+        int tile_m = 128;
         LaunchRec rec;
         if (r == R_ATTN_F32_MFMA) {
             SdpaParams sp{};
-            const int qw = attn_f32_queries(1, L, d);
-            // one workgroup per CU: two waves per SIMD with 256 queries, one with
-            // 128 (two there, of half the keys, cost more partials than they gain)
-            attn_f32_splits(L, (L + qw - 1) / qw * (qw / 128), 2 * qw, &splits, &kps);
+            const AttnF32Shape sh = attn_f32_shape(false, 1, L, d, false);
+            splits = sh.splits;
+            kps = sh.kps;
             sp.L = (int32_t)L; sp.d = (int32_t)d; sp.BH = 1;
             sp.splits = (int32_t)splits; sp.keys_per_split = (int32_t)kps;
-            if (!build_attn_b3(sp, false, &rec))
+            tile_m = sh.queries;
+            if (!build_attn_b3(sp, false, sh.queries, &rec))
                 return fail(QX_ERR_UNSUPPORTED, "no attention kernel for d = %lld", (long long)d);
             rec.bind(offsetof(SdpaParams, Q), BIND_IN0);
             rec.bind(offsetof(SdpaParams, K), BIND_IN1);
@@ -1412,7 +1463,7 @@ qx_status plan_attn(Plan* pl, int32_t dt, int64_t L, int64_t d, int32_t bound, i
             rec.bind(offsetof(AttnParams, O), BIND_OUT);
             pl->launches.push_back(rec);
         }
-        info.tile_m = 128; info.tile_n = (int32_t)d; info.tile_k = (int32_t)kps;
+        info.tile_m = tile_m; info.tile_n = (int32_t)d; info.tile_k = (int32_t)kps;
     }
     info.kernels = (int32_t)pl->launches.size();
     info.workspace_bytes = (int64_t)ws;
@@ -1443,18 +1494,15 @@ qx_status plan_sdpa(Plan* pl, int64_t BH, int64_t L, int64_t d, float scale, int
         info.workspace_bytes = 0;
         return QX_OK;
     }
-    // Key splits only while the query blocks of all heads leave the chip short
-    // of 512 groups of four waves (two per SIMD).
-    const int qw = attn_f32_queries(BH, L, d);
-    int64_t splits, kps;
-    attn_f32_splits(L, (L + qw - 1) / qw * (qw / 128) * BH, 512, &splits, &kps);
+    const AttnF32Shape sh = attn_f32_shape(true, BH, L, d, causal != 0);
+    const int64_t splits = sh.splits, kps = sh.kps;
     SdpaParams a{};
     a.L = (int32_t)L; a.d = (int32_t)d; a.BH = (int32_t)BH;
     a.splits = (int32_t)splits; a.keys_per_split = (int32_t)kps;
     a.causal = causal;
     a.c = (float)((double)scale * 1.4426950408889634);   // log2(e)
     LaunchRec rec;
-    if (!build_attn_b3(a, true, &rec)) return fail(QX_ERR_UNSUPPORTED, "no attention kernel for d = %lld", (long long)d);
+    if (!build_attn_b3(a, true, sh.queries, &rec)) return fail(QX_ERR_UNSUPPORTED, "no attention kernel for d = %lld", (long long)d);
     rec.bind(offsetof(SdpaParams, Q), BIND_IN0);
     rec.bind(offsetof(SdpaParams, K), BIND_IN1);
     rec.bind(offsetof(SdpaParams, V), BIND_IN2);
@@ -1479,7 +1527,7 @@ qx_status plan_sdpa(Plan* pl, int64_t BH, int64_t L, int64_t d, float scale, int
     } else {
         pl->launches.push_back(rec);
     }
-    info.tile_m = qw; info.tile_n = (int32_t)d; info.tile_k = (int32_t)kps;
+    info.tile_m = sh.queries; info.tile_n = (int32_t)d; info.tile_k = (int32_t)kps;
     info.kernels = (int32_t)pl->launches.size();
     info.workspace_bytes = (int64_t)ws;
     return QX_OK;

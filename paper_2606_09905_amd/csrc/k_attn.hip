@@ -672,12 +672,15 @@ __global__ __launch_bounds__(512) void k_attn_i32s(const AttnParams p) {
 //
 // Bound: the matrix cores; per 32x32 block and wave 2048 matrix cycles against
 // about 1450 of vector ALU (exponentials, splits).  32 causal heads x 4096 x
-// 64: 444 us, d = 128, 16 x 2048: 243 (616 and 302 on v_mfma_f32_32x32x2f32);
-// the core at L = 4096, d = 64 40 us (43); errors a third of theirs.  Without
-// the products m l and l m and with one running sum (338, 195 and 33 us) a
-// sum of one product was up to 1.4 ulp off.  The software pipeline (PIPE) is
-// the core's for d <= 64: the softmax form measured 4% slower with it, and
-// d >= 96 has no registers for it.
+// 64: 430 us, 16 x 2048 x 128 235 (616 and 302 on v_mfma_f32_32x32x2f32); the
+// core at L = 4096, d = 64 38.5 us (43), 300 x 64 9.1 (9.3), 2048 x 128 31 (32);
+// errors a third of theirs.  Without the products m l and l m and with one
+// running sum (338, 195 and 33 us) a sum of one product was up to 1.4 ulp off.
+//
+// PIPE, a software pipeline over the blocks, is the core's for d <= 64 with one
+// wave per SIMD and at least eight blocks a split (L = 4096, d = 64 40.1 us
+// without it, 38.5 with; short calls would stage blocks that are not there, 208 x
+// 64 10.5 us with it, 8.7 without; the softmax form lost 4%).
 //
 // Softmax: per block the running maximum m (base-2 exponent domain,
 // t = scale*log2(e)*s) and the running sum are updated online.  With key
@@ -686,7 +689,7 @@ __global__ __launch_bounds__(512) void k_attn_i32s(const AttnParams p) {
 // the partials in split order), so repeated runs are bit-identical.
 // RAG: d < D, columns d..D-1 read as zeros and are not written.
 // ---------------------------------------------------------------------------
-template <int D, int NW, bool SM, bool RAG>
+template <int D, int NW, bool SM, bool RAG, bool PIPE = false>
 __global__ __launch_bounds__(NW * 64) void k_attn_b3(const SdpaParams p) {
     constexpr int NTH = NW * 64;
     constexpr int QW = 32 * NW;              // queries per workgroup
@@ -694,9 +697,10 @@ __global__ __launch_bounds__(NW * 64) void k_attn_b3(const SdpaParams p) {
     constexpr int NTO = D / 32;              // output row tiles of O^T
     constexpr int KP = 2 * D + 16;           // bytes of a K row and of a V column in LDS (padded:
     constexpr int VP = 2 * AKB + 16;         // 16 rows of one chunk fall on 64 different banks)
+    constexpr bool FROM_ZERO = SM || (D <= 64 && !PIPE);
+    static_assert(!PIPE || !SM, "the pipeline has no place for the running maximum");
     constexpr int KB = AKB * KP, VB = D * VP;            // bytes of one plane
     constexpr int NI = (8 * D + NTH - 1) / NTH;          // staging items (8 elements) per thread
-    constexpr bool PIPE = !SM && D <= 64;
     __shared__ __align__(16) unsigned char lds[2][3 * (KB + VB)];
     __shared__ int large_k;
 
@@ -762,9 +766,9 @@ __global__ __launch_bounds__(NW * 64) void k_attn_b3(const SdpaParams p) {
         }
         if (SM) asm volatile("" : "+v"(qmax));   // found here, not from values kept to the end
     }
-    f16x o[NTO], low[NTO];            // low: PIPE only
+    f16x o[NTO];
 #pragma unroll
-    for (int n = 0; n < NTO; ++n) o[n] = low[n] = f16x{};
+    for (int n = 0; n < NTO; ++n) o[n] = f16x{};
     float m = -INFINITY;              // running maximum of t for query q
     float lsum = 0.f;                 // this half's share of the running sum
 
@@ -777,8 +781,8 @@ __global__ __launch_bounds__(NW * 64) void k_attn_b3(const SdpaParams p) {
     // column, so no load is guarded: the scores of such keys are masked, Q is
     // 0 in such columns and O's are not written.
     typedef float Stage[NI][8];
-    auto load = [&](Stage& st, int jk, int jv) {
-        const int kk = key_lo + min(jk, nblk - 1) * AKB, kv = key_lo + min(jv, nblk - 1) * AKB;
+    auto load = [&](Stage& st, int jk, int jv) {   // block jk of K, jv of V
+        const int kk = key_lo + jk * AKB, kv = key_lo + jv * AKB;
         const float* Kb = Kp + (int64_t)kk * d;
         const float* Vb = Vp + (int64_t)kv * d;
         const int last_k = key_hi - 1 - kk, last_v = key_hi - 1 - kv;
@@ -803,7 +807,7 @@ __global__ __launch_bounds__(NW * 64) void k_attn_b3(const SdpaParams p) {
             }
         }
     };
-    // block jk of K into buffer jk & 1 and block jv of V into buffer jv & 1
+    // block j into buffer j & 1
     auto stash = [&](const Stage& st, int jk, int jv) {
 #pragma unroll
         for (int i = 0; i < NI; ++i) {
@@ -819,8 +823,7 @@ __global__ __launch_bounds__(NW * 64) void k_attn_b3(const SdpaParams p) {
             }
             b8 a, b, l;
             split3(v, a, b, l);
-            unsigned char* dst = is_k ? &lds[jk & 1][(it / (D / 8)) * KP + it % (D / 8) * 16]
-                                      : &lds[jv & 1][3 * KB + (iv % D) * VP + iv / D * 16];
+            unsigned char* dst = &lds[(is_k ? jk : jv) & 1][is_k ? (it / (D / 8)) * KP + it % (D / 8) * 16 : 3 * KB + (iv % D) * VP + iv / D * 16];
             const int plane = is_k ? KB : VB;
             *(b8*)dst = a;
             *(b8*)(dst + plane) = b;
@@ -842,7 +845,7 @@ __global__ __launch_bounds__(NW * 64) void k_attn_b3(const SdpaParams p) {
 #undef QX_S
         }
         s += slow;
-        if (!PIPE) __builtin_amdgcn_sched_barrier(0);
+        if (D > 64) __builtin_amdgcn_sched_barrier(0);
     };
     // the same from the caller's arrays, on the fp32 matrix cores
     auto scores_f32 = [&](int j, f16x& s) {
@@ -907,16 +910,19 @@ __global__ __launch_bounds__(NW * 64) void k_attn_b3(const SdpaParams p) {
             split3(pv, ph[t], pm[t], pl[t]);
         }
     };
-    // O^T = alpha O^T + V^T S^T of block j.  The h h products and the smaller
-    // ones are kept apart, by the pipelined core in o and low all the way,
-    // else in sums over the block.
+    // O^T = alpha O^T + V^T S^T of block j, the smaller products and the h h
+    // ones summed apart, each from zero.  The core adds the latter straight to
+    // O in long sums and where registers are short (d >= 96): a matrix step
+    // cuts its addend at 2^-25 of its largest product, which a short sum that
+    // cancels shows (160 x 32: largest error 1.1e-6 of the rms so, 3.9e-7 from
+    // zero; 6.6e-7 on the fp32 matrix cores).
     auto accumulate = [&](int j, const b8 (&ph)[2], const b8 (&pm)[2], const b8 (&pl)[2]) {
         const unsigned char* Vs = &lds[j & 1][3 * KB + l32 * VP + 16 * h];
-        if (!PIPE) __builtin_amdgcn_sched_barrier(0);
+        if (D > 64) __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
         for (int n = 0; n < NTO; ++n) {
-            f16x high_sum = f16x{}, low_sum = f16x{};
-            f16x &hs = PIPE ? o[n] : high_sum, &ls = PIPE ? low[n] : low_sum;
+            f16x high_sum = f16x{}, ls = f16x{};
+            f16x& hs = FROM_ZERO ? high_sum : o[n];
             b8 vh[2];
 #define QX_PV(S_, V_, P_) S_ = __builtin_amdgcn_mfma_f32_32x32x16_bf16(V_, P_[t], S_, 0, 0, 0);
 #pragma unroll
@@ -930,11 +936,12 @@ __global__ __launch_bounds__(NW * 64) void k_attn_b3(const SdpaParams p) {
 #pragma unroll
             for (int t = 0; t < 2; ++t) QX_PV(hs, vh[t], ph)
 #undef QX_PV
-            if (!PIPE) {
 #pragma unroll
-                for (int r = 0; r < 16; ++r) o[n][r] = (SM ? fmaf(o[n][r], alpha, ls[r]) : o[n][r] + ls[r]) + hs[r];
-                __builtin_amdgcn_sched_barrier(0);
+            for (int r = 0; r < 16; ++r) {
+                const float low = SM ? fmaf(o[n][r], alpha, ls[r]) : o[n][r] + ls[r];
+                o[n][r] = FROM_ZERO ? low + hs[r] : low;
             }
+            if (D > 64) __builtin_amdgcn_sched_barrier(0);
         }
     };
     auto accumulate_f32 = [&](int j, const f16x& s) {
@@ -954,15 +961,26 @@ __global__ __launch_bounds__(NW * 64) void k_attn_b3(const SdpaParams p) {
         }
     };
 
-    // Software pipeline: pass j splits the scores of block j beside the score
-    // products of block j + 1, then stages K of block j + 2 and V of block
-    // j + 1 beside the O products of block j, so each of the vector ALU's
-    // parts runs under matrix products that do not wait for it.  (The last
-    // pass's scores are of a stale block and are not used.)
+    b8 ph[2], pm[2], pl[2];
     Stage st;
-    auto pass = [&](int j, f16x& s, f16x& sn) {
-        b8 ph[2], pm[2], pl[2];
-        if (PIPE) {
+    if constexpr (PIPE) {
+        // Pass j splits the scores of block j beside the score products of
+        // block j + 1, then stages K of block j + 2 and V of block j + 1 beside
+        // the O products of block j.  (Past the last block the last one is
+        // staged again; the last pass's scores are not used.)
+        const int end = nblk - 1;
+        Stage st1;
+        load(st, 0, 0);
+        load(st1, min(1, end), min(1, end));
+        stash(st, 0, 0);
+        stash(st1, 1, 1);
+        load(st, min(2, end), min(1, end));
+        __syncthreads();
+        f16x s0, s1;
+        scores(0, s0);
+        mask(0, s0);
+        __syncthreads();                     // pass 0 stages over K of block 0
+        auto pass = [&](int j, f16x& s, f16x& sn) {
             scores(j + 1, sn);
             split_s(s, ph, pm, pl);
             // all of it before the mask's branch, beside the scores
@@ -971,9 +989,23 @@ __global__ __launch_bounds__(NW * 64) void k_attn_b3(const SdpaParams p) {
             mask(j + 1, sn);
             accumulate(j, ph, pm, pl);
             stash(st, j + 2, j + 1);
-            load(st, j + 3, j + 2);
-        } else {
+            load(st, min(j + 3, end), min(j + 2, end));
+            __syncthreads();
+        };
+        for (int j = 0; j < nblk; j += 2) {
+            pass(j, s0, s1);
+            if (j + 1 < nblk) pass(j + 1, s1, s0);
+        }
+    } else {
+        if (nblk > 0) {
+            load(st, 0, 0);
+            stash(st, 0, 0);
+            if (nblk > 1) load(st, 1, 1);
+            __syncthreads();
+        }
+        for (int j = 0; j < nblk; ++j) {
             if (j < nact) {
+                f16x s;
                 scores(j, s);
                 mask(j, s);
                 if (SM) {
@@ -981,39 +1013,15 @@ __global__ __launch_bounds__(NW * 64) void k_attn_b3(const SdpaParams p) {
                     exponentials(s, kSplitScale);
                 }
                 split_s(s, ph, pm, pl);
+                // (before the products, which do not wait for it)
+                if (j + 1 < nblk) stash(st, j + 1, j + 1);
                 accumulate(j, ph, pm, pl);
+            } else if (j + 1 < nblk) {
+                stash(st, j + 1, j + 1);
             }
-            stash(st, j + 1, j + 1);
-            load(st, j + 2, j + 2);
-        }
-        __syncthreads();
-    };
-    f16x s0 = f16x{}, s1 = f16x{};
-    if (nblk > 0) {
-        load(st, 0, 0);
-        if (PIPE) {
-            Stage st1;
-            load(st1, 1, 1);
-            stash(st, 0, 0);
-            stash(st1, 1, 1);
-            load(st, 2, 1);
-        } else {
-            stash(st, 0, 0);
-            load(st, 1, 1);
-        }
-        __syncthreads();
-        if (PIPE) {
-            scores(0, s0);
-            mask(0, s0);
-            __syncthreads();                 // pass 0 stages over K of block 0
-        }
-        for (int j = 0; j < nblk; j += 2) {
-            pass(j, s0, s1);
-            if (j + 1 < nblk) pass(j + 1, s1, s0);
-        }
-        if (PIPE) {
-#pragma unroll
-            for (int n = 0; n < NTO; ++n) o[n] += low[n];
+            if (j + 1 == nblk) break;
+            if (j + 2 < nblk) load(st, j + 2, j + 2);
+            __syncthreads();
         }
     }
     // Split values are finite only where the products are (f32_split.h): an
@@ -1182,32 +1190,24 @@ void build_reduce(const ReduceParams& p, LaunchRec* rec) {
     rec->set_params(p);
 }
 
-// 256 queries per workgroup share one split of every key block; 128 where
-// that would leave the chip short of workgroups (the core at L = 4096, d = 64
-// 36.4 us with 128 against 38.0, L = 2000, d = 96 27.7 against 33.1; above the
-// line, L = 4096, d = 128 59 us with 256 against 66, 16 softmax heads of
-// 4096 x 64 344 against 375) or more than a fifth of the rows empty (128 causal
-// heads of 128 13.2 against 14.6).
-int attn_f32_queries(int64_t BH, int64_t L, int64_t d) {
-    return BH * L * d > (1 << 18) && (L + 255) / 256 * 256 * 4 <= 5 * L ? 256 : 128;
-}
-
 template <int D, bool SM>
-static const void* attn_b3_fn(int queries, bool rag) {
+static const void* attn_b3_fn(int queries, bool rag, bool pipe) {
+    if constexpr (!SM && D <= 64)
+        if (pipe) return (const void*)k_attn_b3<D, 4, false, false, true>;
     if (queries == 256) return rag ? (const void*)k_attn_b3<D, 8, SM, SM> : (const void*)k_attn_b3<D, 8, SM, false>;
     return rag ? (const void*)k_attn_b3<D, 4, SM, SM> : (const void*)k_attn_b3<D, 4, SM, false>;
 }
 
-bool build_attn_b3(const SdpaParams& p, bool softmax, LaunchRec* rec) {
+bool build_attn_b3(const SdpaParams& p, bool softmax, int queries, LaunchRec* rec) {
     const int D = (p.d + 31) / 32 * 32;
     const bool rag = p.d != D;
-    const int queries = attn_f32_queries(p.BH, p.L, p.d);
     if (rag && !softmax) return false;
+    const bool pipe = !softmax && queries == 128 && p.keys_per_split >= 8 * AKB && p.L >= 8 * AKB;
     switch (D) {
-    case 32: rec->fn = softmax ? attn_b3_fn<32, true>(queries, rag) : attn_b3_fn<32, false>(queries, rag); break;
-    case 64: rec->fn = softmax ? attn_b3_fn<64, true>(queries, rag) : attn_b3_fn<64, false>(queries, rag); break;
-    case 96: rec->fn = softmax ? attn_b3_fn<96, true>(queries, rag) : attn_b3_fn<96, false>(queries, rag); break;
-    case 128: rec->fn = softmax ? attn_b3_fn<128, true>(queries, rag) : attn_b3_fn<128, false>(queries, rag); break;
+    case 32: rec->fn = softmax ? attn_b3_fn<32, true>(queries, rag, pipe) : attn_b3_fn<32, false>(queries, rag, pipe); break;
+    case 64: rec->fn = softmax ? attn_b3_fn<64, true>(queries, rag, pipe) : attn_b3_fn<64, false>(queries, rag, pipe); break;
+    case 96: rec->fn = softmax ? attn_b3_fn<96, true>(queries, rag, pipe) : attn_b3_fn<96, false>(queries, rag, pipe); break;
+    case 128: rec->fn = softmax ? attn_b3_fn<128, true>(queries, rag, pipe) : attn_b3_fn<128, false>(queries, rag, pipe); break;
     default: return false;
     }
     rec->name = softmax ? "sdpa_f32" : "attn_f32";

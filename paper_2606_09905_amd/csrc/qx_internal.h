@@ -402,10 +402,9 @@ bool build_attn_i32r(const AttnParams& p, LaunchRec* rec);
 // d in {32, 64}, keys_per_split a multiple of 128, V8 block-major
 bool build_attn_i32s(const AttnParams& p, LaunchRec* rec);
 void build_reduce(const ReduceParams& p, LaunchRec* rec);
-// FP32 attention (the core, d in {32, 64, 96, 128}, or softmax, d <= 128) and
-// the queries per workgroup it takes
-int attn_f32_queries(int64_t BH, int64_t L, int64_t d);
-bool build_attn_b3(const SdpaParams& p, bool softmax, LaunchRec* rec);
+// FP32 attention (the core, d in {32, 64, 96, 128}, or softmax, d <= 128), 128
+// or 256 queries per workgroup
+bool build_attn_b3(const SdpaParams& p, bool softmax, int queries, LaunchRec* rec);
 void build_sdpa_combine(const SdpaCombineParams& p, LaunchRec* rec);
 void build_fill(const FillParams& p, LaunchRec* rec);
 void build_range(const RangeParams& p, LaunchRec* rec);

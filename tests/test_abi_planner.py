@@ -103,6 +103,21 @@ def test_limb_routes_take_the_encode_nt_structure_when_large():
     assert qx.plan_gemm_i16i32(64, 64, 64, 1, 127, 127)["kernels"] == 1
 
 
+# FP32 attention: queries per workgroup and key splits.  Short calls split down
+# to a 32-key block; workgroups fill whole rounds of the 256 CUs, not a few more.
+@pytest.mark.parametrize("BH,L,d,splits", [(None, 208, 96, 7), (None, 300, 64, 10), (None, 64, 32, 1), (None, 4096, 64, None),
+                                           (None, 3693, 64, None), (3, 128, 64, 4), (128, 128, 64, 1), (2, 7878, 64, 4)])
+def test_attn_f32_shapes(BH, L, d, splits):
+    p = qx.plan_attn("f32", L, d) if BH is None else qx.plan_sdpa_f32(BH, L, d, 0.125, False)
+    n = -(-L // p["tile_k"])
+    assert p["tile_m"] in (128, 256) and p["tile_k"] % 32 == 0
+    assert splits is None or n == splits, p
+    assert p["kernels"] == (2 if n > 1 else 1)
+    assert p["workspace_bytes"] >= (4 * n * (BH or 1) * L * d if n > 1 else 0)
+    wgs = -(-L // p["tile_m"]) * (BH or 1) * n
+    assert wgs <= 256 or wgs % 256 == 0 or wgs % 256 > 128, wgs
+
+
 # INT32 convolutions of at most 16 channels: direct (one launch, no workspace)
 # while the walk over the sum is short for its pixels, else through the limbs
 @pytest.mark.parametrize("N,Ci,H,Co,k,stride,direct", [
