@@ -142,7 +142,9 @@ int32_t products_of(int32_t r) {
     switch (r) {
     case R_I8_KARATSUBA: return 3;
     case R_I8_OFFSET4: return 4;
-    case R_S24_I8LIMB: return 8;
+    case R_S24_I8LIMB:
+    case R_ATTN_F32_MFMA:
+    case R_F32_MFMA: return 8;
     case R_ATTN_I32_MFMA: return 3;
     default: return 1;
     }
@@ -840,9 +842,9 @@ qx_status plan_conv_t(Plan* pl, int32_t dt, int64_t N, int64_t Ci, int64_t H, in
         if (r != R_F32_MFMA && r != R_F32_VALU)
             return fail(QX_ERR_INVALID_ARG, "route %d does not apply to an FP32 convolution", route);
         if (r == R_F32_MFMA && !mfma_ok)
-            return fail(QX_ERR_UNSUPPORTED, "the fp32 MFMA convolution needs C_in a multiple of 32");
+            return fail(QX_ERR_UNSUPPORTED, "the matrix-core FP32 convolution needs C_in a multiple of 32");
         info.route = r;
-        info.products = 1;
+        info.products = products_of(r);
         info.chunk = 0;
         info.exact_no_wrap = 0;
         if (N == 0 || Co == 0) {
@@ -1288,7 +1290,7 @@ qx_status plan_attn(Plan* pl, int32_t dt, int64_t L, int64_t d, int32_t bound, i
         if (r != R_ATTN_F32_MFMA && r != R_ATTN_F32_VALU)
             return fail(QX_ERR_INVALID_ARG, "route %d does not apply to FP32 attention", route);
         if (r == R_ATTN_F32_MFMA && !mfma_shape)
-            return fail(QX_ERR_UNSUPPORTED, "fp32 MFMA attention needs d in {32, 64, 96, 128}");
+            return fail(QX_ERR_UNSUPPORTED, "matrix-core FP32 attention needs d in {32, 64, 96, 128}");
         info.exact_no_wrap = 0;
     } else {
         const int64_t b = bound == 0 ? ((int64_t)1 << 31) : bound;
@@ -1303,7 +1305,7 @@ qx_status plan_attn(Plan* pl, int32_t dt, int64_t L, int64_t d, int32_t bound, i
         info.exact_no_wrap = ((double)L * (double)d * (double)b * (double)b * (double)b < 2147483648.0) ? 1 : 0;
     }
     info.route = r;
-    info.products = r == R_ATTN_I32_MFMA ? 3 : 1;
+    info.products = products_of(r);
     info.chunk = 0;
     if (L == 0 || d == 0) {
         info.kernels = 0;
@@ -1339,13 +1341,41 @@ qx_status plan_attn(Plan* pl, int32_t dt, int64_t L, int64_t d, int32_t bound, i
         pl->launches.push_back(r1);
         pl->launches.push_back(r2);
         info.tile_m = 64; info.tile_n = 64; info.tile_k = 16;
+    } else if (r == R_ATTN_F32_MFMA) {
+        SdpaParams sp{};
+        LaunchRec rec;
+        const AttnF32Shape sh = attn_f32_shape(false, 1, L, d, false);
+        const int64_t splits = sh.splits, kps = sh.kps;
+        sp.L = (int32_t)L; sp.d = (int32_t)d; sp.BH = 1;
+        sp.splits = (int32_t)splits; sp.keys_per_split = (int32_t)kps;
+        if (!build_attn_b3(sp, false, sh.queries, &rec))
+            return fail(QX_ERR_UNSUPPORTED, "no attention kernel for d = %lld", (long long)d);
+        rec.bind(offsetof(SdpaParams, Q), BIND_IN0);
+        rec.bind(offsetof(SdpaParams, K), BIND_IN1);
+        rec.bind(offsetof(SdpaParams, V), BIND_IN2);
+        rec.bind(offsetof(SdpaParams, O), BIND_OUT);
+        if (splits > 1) {
+            ws = 4 * (uint64_t)splits * (uint64_t)L * (uint64_t)d;
+            rec.bind(offsetof(SdpaParams, part), BIND_WS, 0);
+            pl->launches.push_back(rec);
+            ReduceParams rp{};
+            rp.n = rp.stride = L * d;
+            rp.splits = (int32_t)splits;
+            LaunchRec rr;
+            build_reduce(rp, &rr);
+            rr.bind(offsetof(ReduceParams, part), BIND_WS, 0);
+            rr.bind(offsetof(ReduceParams, out), BIND_OUT);
+            pl->launches.push_back(rr);
+        } else {
+            pl->launches.push_back(rec);
+        }
+        info.tile_m = sh.queries; info.tile_n = (int32_t)d; info.tile_k = (int32_t)kps;
     } else {
         // Key splits: enough workgroups for one per CU (>= 256), split
         // boundaries on 32-key blocks.  Twice that many (shorter splits)
         // measured 10% slower on L = 4096, d = 64 (more per-workgroup
-        // set-up and more partial outputs to combine); half as many left
-        // CUs idle (FP32 1.6x slower).
-        const bool stream = r == R_ATTN_I32_MFMA && (d == 32 || d == 64);
+        // set-up and more partial outputs to combine).
+        const bool stream = d == 32 || d == 64;
         const int qt = stream ? attn_stream_qt(L) : 4;       // query tiles of 32 per workgroup
         const int64_t qgroups = (L + 32 * qt - 1) / (32 * qt);
         const int64_t kblocks = (L + 31) / 32;
@@ -1356,7 +1386,7 @@ qx_status plan_attn(Plan* pl, int32_t dt, int64_t L, int64_t d, int32_t bound, i
             // number of whole 32-key blocks
             const int64_t g = 64 * (8 / qt);
             kps = (kps + g - 1) / g * g;
-        } else if (r == R_ATTN_I32_MFMA && d == 128) {
+        } else if (d == 128) {
             // resident splits: kps * d a multiple of 4096 (whole 1 KB loads
             // per wave) and both int8 tiles within 48 KiB of LDS
             const int64_t g = std::max<int64_t>(32, 4096 / d), cap = 24576 / d / g * g;
@@ -1367,38 +1397,8 @@ qx_status plan_attn(Plan* pl, int32_t dt, int64_t L, int64_t d, int32_t bound, i
         a.L = (int32_t)L; a.d = (int32_t)d; a.splits = (int32_t)splits; a.keys_per_split = (int32_t)kps;
         a.limbs = 3;
         a.qt = qt;
-        int tile_m = 128;
         LaunchRec rec;
-        if (r == R_ATTN_F32_MFMA) {
-            SdpaParams sp{};
-            const AttnF32Shape sh = attn_f32_shape(false, 1, L, d, false);
-            splits = sh.splits;
-            kps = sh.kps;
-            sp.L = (int32_t)L; sp.d = (int32_t)d; sp.BH = 1;
-            sp.splits = (int32_t)splits; sp.keys_per_split = (int32_t)kps;
-            tile_m = sh.queries;
-            if (!build_attn_b3(sp, false, sh.queries, &rec))
-                return fail(QX_ERR_UNSUPPORTED, "no attention kernel for d = %lld", (long long)d);
-            rec.bind(offsetof(SdpaParams, Q), BIND_IN0);
-            rec.bind(offsetof(SdpaParams, K), BIND_IN1);
-            rec.bind(offsetof(SdpaParams, V), BIND_IN2);
-            rec.bind(offsetof(SdpaParams, O), BIND_OUT);
-            if (splits > 1) {
-                ws = 4 * (uint64_t)splits * (uint64_t)L * (uint64_t)d;
-                rec.bind(offsetof(SdpaParams, part), BIND_WS, 0);
-                pl->launches.push_back(rec);
-                ReduceParams rp{};
-                rp.n = rp.stride = L * d;
-                rp.splits = (int32_t)splits;
-                LaunchRec rr;
-                build_reduce(rp, &rr);
-                rr.bind(offsetof(ReduceParams, part), BIND_WS, 0);
-                rr.bind(offsetof(ReduceParams, out), BIND_OUT);
-                pl->launches.push_back(rr);
-            } else {
-                pl->launches.push_back(rec);
-            }
-        } else if (stream) {
+        if (stream) {
             // prep: int8 K rows and block-major int8 V in the workspace, O
             // cleared for split accumulation; then eight waves per
             // workgroup stream their keys from them (no LDS staging)
@@ -1463,7 +1463,7 @@ qx_status plan_attn(Plan* pl, int32_t dt, int64_t L, int64_t d, int32_t bound, i
             rec.bind(offsetof(AttnParams, O), BIND_OUT);
             pl->launches.push_back(rec);
         }
-        info.tile_m = tile_m; info.tile_n = (int32_t)d; info.tile_k = (int32_t)kps;
+        info.tile_m = 128; info.tile_n = (int32_t)d; info.tile_k = (int32_t)kps;
     }
     info.kernels = (int32_t)pl->launches.size();
     info.workspace_bytes = (int64_t)ws;
@@ -1486,7 +1486,7 @@ qx_status plan_sdpa(Plan* pl, int64_t BH, int64_t L, int64_t d, float scale, int
     pl->in_align = d % 32 == 0 ? 16 : 4;
     qx_plan_info& info = pl->info;
     info.route = R_ATTN_F32_MFMA;
-    info.products = 1;
+    info.products = products_of(R_ATTN_F32_MFMA);
     info.chunk = 0;
     info.exact_no_wrap = 0;
     if (BH == 0 || L == 0 || d == 0) {

@@ -112,7 +112,7 @@ def test_attn_f32_shapes(BH, L, d, splits):
     n = -(-L // p["tile_k"])
     assert p["tile_m"] in (128, 256) and p["tile_k"] % 32 == 0
     assert splits is None or n == splits, p
-    assert p["kernels"] == (2 if n > 1 else 1)
+    assert p["kernels"] == (2 if n > 1 else 1) and p["products"] == 8
     assert p["workspace_bytes"] >= (4 * n * (BH or 1) * L * d if n > 1 else 0)
     wgs = -(-L // p["tile_m"]) * (BH or 1) * n
     assert wgs <= 256 or wgs % 256 == 0 or wgs % 256 > 128, wgs
@@ -132,11 +132,12 @@ def test_conv_i32_few_channel_routes(N, Ci, H, Co, k, stride, direct):
 
 
 def test_conv_f32_i32_plans():
-    # FP32: the fp32 matrix cores when C_in % 32 == 0 (prep launch + gathering
-    # NT GEMM), else explicit lowering + vector-ALU fp32 GEMM
+    # FP32: the bf16 matrix cores when C_in % 32 == 0 (a launch that splits x
+    # and w into three bf16 terms, 6 bytes an element, + the gathering
+    # contraction of eight products), else explicit lowering + vector-ALU GEMM
     p = qx.plan_conv2d_t("f32", 8, 64, 56, 56, 128, 3, 3, 1, 1)
-    assert p["route_name"] == "f32_mfma" and p["kernels"] == 2
-    assert p["workspace_bytes"] >= 4 * 8 * 58 * 58 * 64 + 4 * 128 * 576
+    assert p["route_name"] == "f32_mfma" and p["kernels"] == 2 and p["products"] == 8
+    assert p["workspace_bytes"] >= 6 * 8 * 58 * 58 * 64 + 6 * 128 * 576
     p = qx.plan_conv2d_t("f32", 2, 3, 20, 20, 8, 3, 3, 1, 1)
     assert p["route_name"] == "f32_valu" and p["kernels"] == 2
     with pytest.raises(qx.QxError) as e:
