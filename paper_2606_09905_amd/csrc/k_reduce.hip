@@ -117,15 +117,9 @@ __global__ __launch_bounds__(RT) void k_minmax_final(const MinMaxParams p) {
 // greater (row-major window order).
 // ---------------------------------------------------------------------------
 template <bool AVG>
-__device__ __forceinline__ uint32_t pool4(const uint32_t* a, const uint32_t* b, bool relu) {
+__device__ __forceinline__ uint32_t pool4(const uint32_t* a, const uint32_t* b) {
     if (AVG) {
-        int64_t v0 = (int32_t)a[0], v1 = (int32_t)a[1], v2 = (int32_t)b[0], v3 = (int32_t)b[1];
-        if (relu) {
-            v0 = v0 > 0 ? v0 : 0;
-            v1 = v1 > 0 ? v1 : 0;
-            v2 = v2 > 0 ? v2 : 0;
-            v3 = v3 > 0 ? v3 : 0;
-        }
+        const int64_t v0 = (int32_t)a[0], v1 = (int32_t)a[1], v2 = (int32_t)b[0], v3 = (int32_t)b[1];
         return (uint32_t)(int32_t)((v0 + v1 + v2 + v3) >> 2);
     }
     float m = __uint_as_float(a[0]);
@@ -158,10 +152,10 @@ __global__ __launch_bounds__(RT) void k_pool2(const PoolParams p) {
                                (uint32_t)b1[0], (uint32_t)b1[1], (uint32_t)b1[2], (uint32_t)b1[3]};
         i4v o;
 #pragma unroll
-        for (int e = 0; e < 4; ++e) o[e] = (int)pool4<AVG>(a + 2 * e, b + 2 * e, p.relu);
+        for (int e = 0; e < 4; ++e) o[e] = (int)pool4<AVG>(a + 2 * e, b + 2 * e);
         *(i4v*)out = o;
     } else {
-        for (int e = 0; e < 4 && ow0 + e < p.Wo; ++e) out[e] = pool4<AVG>(row0 + 2 * e, row1 + 2 * e, p.relu);
+        for (int e = 0; e < 4 && ow0 + e < p.Wo; ++e) out[e] = pool4<AVG>(row0 + 2 * e, row1 + 2 * e);
     }
 }
 

@@ -96,7 +96,7 @@ struct EncParams {
     int32_t batch;
     int32_t vec;            // fp16 encoders: rows and batch strides allow 16-byte source loads
                             // (the limb encoders load vectors at any alignment: 1000x777x1501
-                            // offset limbs 26.4 -> 23.1 us a step; here that measured 4% slower
+                            // offset limbs 26.3 -> 22.8 us a step; here that measured 4% slower
                             // on 1001x2043x1999)
     int32_t* sums;          // int8 limb routes with an offset: row sums [batch][M] of A
                             // (A encoder) or per-64-k-slice column sums [batch][Kp/64][N]
@@ -282,7 +282,6 @@ struct PoolParams {
     int64_t NC;
     int32_t H, W, Ho, Wo;
     int32_t vec;            // W % 8 == 0: 16-byte loads and stores
-    int32_t relu;           // average of max(x, 0) (a ReLU fused ahead of the pool)
 };
 
 // In-place ReLU of int32 values: p[i] = max(p[i], 0).
