@@ -1380,8 +1380,11 @@ static bool aligned_for(const GemmParams& p, int elem, int bvec) {
 
 // The register-staged kernels take 64 x 64 tiles where 128 x 128 ones would
 // be fewer than 64 or more than half empty.
+static bool few_tiles(int64_t M, int64_t N, int64_t batch) {
+    return ((M + 127) / 128) * ((N + 127) / 128) * batch < 64;
+}
 static bool reg_staged_small(int64_t M, int64_t N, int64_t batch) {
-    return M <= 64 || N <= 64 || ((M + 127) / 128) * ((N + 127) / 128) * batch < 64;
+    return M <= 64 || N <= 64 || few_tiles(M, N, batch);
 }
 
 // K slices of a register-staged kernel (grid y, added into a cleared C): one
@@ -1417,8 +1420,13 @@ bool build_gemm_mfma(int32_t route, const GemmParams& p, int batch, LaunchRec* r
         if (reg_staged_small(p.M, p.N, batch)) {
             *tile_m = 64;
             *tile_n = 64;
-            // K within four tiles: 32 x 32 tiles, K split over the four waves
-            if (p.K <= 4 * 64) {
+            // K within four tiles: 32 x 32 tiles, K split over the four waves,
+            // but not for many tiles, nor for short K, which leaves half of the
+            // waves without a part (32 x 32 / 64 x 64 tiles: 20 x (6087x49x48)
+            // 62 / 22 us, 3 x (4000x50x128) 13.1 / 7.0, 20 x (6087x49x200) 151 /
+            // 59; 64 x (200x64x200) 6.9 / 10.2, 8192x64x200 5.2 / 10.0)
+            const int64_t tiles = (int64_t)((p.M + 63) / 64) * ((p.N + 63) / 64) * batch;
+            if (p.K <= 4 * 64 && (few_tiles(p.M, p.N, batch) || (p.K > 2 * 64 && tiles <= 512))) {
                 *tile_m = 32;
                 *tile_n = 32;
                 if (al && !step) fill_gemm_rec(rec, k_gemm_f16_ks<true, false>, p, 32, 32, batch, "gemm_f16_ksplit");
