@@ -241,18 +241,21 @@ qx_status plan_int_gemm(const GemmSpec& s, Plan* pl, uint64_t* ws_used) {
             // path: large problems take three int8 products instead (bounds
             // 1024, 3x(2435x528x4671) 672 / 224 us, 1000x777x500 22.1 / 15.3;
             // below the line 512^3 10.8 / 12.2, 2048x2048x128 13.0 / 14.3),
-            // but not where the fp16 kernel slices K and the operands are too
-            // much to encode for their use: few tiles (33x33x250000 58 / 386,
-            // 54x362x14648 24 / 34, 256x256x8192 21 / 27; above 16 tiles
-            // 68x743x8110 36 / 30) or one short side (64x8192x8192 112 / 138,
-            // 48x6000x1000 17 / 21; 102x1960x2522 32 / 24).
+            // but not where the operands are too much to encode for their use:
+            // K sliced over few tiles (33x33x250000 58 / 386, 54x362x14648 24 /
+            // 34, 256x256x8192 21 / 27; above 16 tiles 68x743x8110 36 / 30), or
+            // a short side (64x8192x8192 112 / 138, 48x6000x1000 17 / 21, 64 x
+            // (130x64x512) 16 / 33, 300 x (64x64x1024) 48 / 129, 8 x
+            // (8192x64x448) 44 / 53; longer sums 102x1960x2522 32 / 24, 22 x
+            // (96x80x1720) 32 / 27, 9 x (61x1899x7424) 473 / 328).
             if (route == R_F16_EXACT && f16_chunk(s.ba, s.bb) < 64 && feasible_i16(R_I8_KARATSUBA, s.ba, s.bb) &&
                 s.allow_nt && s.K >= 256 && use_i8nt(R_I8_KARATSUBA, s.M, s.N, s.K, s.batch) &&
                 (double)s.M * (double)s.N * (double)s.K * (double)s.batch >= (double)(1 << 28)) {
                 const int64_t Mp = pad_up(s.M, 64), Np = pad_up(s.N, 64), tiles = Mp / 64 * (Np / 64) * s.batch;
                 const bool sliced = dense_out(s) && reg_staged_ksplit(R_F16_EXACT, s.M, s.N, s.K, s.batch) > 1;
-                const bool short_side = s.batch == 1 && tiles >= 64 && Mp * Np <= 100 * (s.M + s.N);
-                if (!sliced || (tiles > 16 && !short_side)) route = R_I8_KARATSUBA;
+                const bool short_side = Mp * Np <= 100 * (s.M + s.N) &&
+                                        (s.K <= (sliced ? 768 : 2048) || (sliced && s.batch == 1 && tiles >= 64));
+                if (!short_side && !(sliced && tiles <= 16)) route = R_I8_KARATSUBA;
             }
         }
         if (!route_applies_i16(route))
