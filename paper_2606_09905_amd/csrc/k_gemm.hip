@@ -1420,13 +1420,13 @@ bool build_gemm_mfma(int32_t route, const GemmParams& p, int batch, LaunchRec* r
         if (reg_staged_small(p.M, p.N, batch)) {
             *tile_m = 64;
             *tile_n = 64;
-            // K within four tiles: 32 x 32 tiles, K split over the four waves,
-            // but not for many tiles, nor for short K, which leaves half of the
-            // waves without a part (32 x 32 / 64 x 64 tiles: 20 x (6087x49x48)
-            // 62 / 22 us, 3 x (4000x50x128) 13.1 / 7.0, 20 x (6087x49x200) 151 /
-            // 59; 64 x (200x64x200) 6.9 / 10.2, 8192x64x200 5.2 / 10.0)
-            const int64_t tiles = (int64_t)((p.M + 63) / 64) * ((p.N + 63) / 64) * batch;
-            if (p.K <= 4 * 64 && (few_tiles(p.M, p.N, batch) || (p.K > 2 * 64 && tiles <= 512))) {
+            // K within four tiles: 32 x 32 tiles, K split over the four waves.
+            // With many tiles only where its loads are whole vectors and K
+            // feeds two waves or 64 x 64 tiles would be half empty (32 x 32 /
+            // 64 x 64 tiles, us: 20 x (6080x48x192) 29 / 45, 1000 x (64x64x96)
+            // 17.8 / 17.6, 87 x (17x1176x48) 12.4 / 18; 20 x (6080x48x64) 26 /
+            // 20, 20 x (6087x49x48) 62 / 22, 1000 x (60x60x200) 103 / 34).
+            if (p.K <= 4 * 64 && (few_tiles(p.M, p.N, batch) || (al && (p.K > 64 || std::min(p.M, p.N) <= 32)))) {
                 *tile_m = 32;
                 *tile_n = 32;
                 if (al && !step) fill_gemm_rec(rec, k_gemm_f16_ks<true, false>, p, 32, 32, batch, "gemm_f16_ksplit");

@@ -13,7 +13,7 @@ torch = pytest.importorskip("torch")
 # batch, M, N, K: below and from eight K tiles, slices with a short last one,
 # one row or column, many tiles (no slices), 128 x 128 tiles, K within 32
 SHAPES = [(1, 1, 1, 448), (1, 1, 1, 449), (1, 20, 48, 4096), (1, 65, 63, 1001), (3, 22, 20, 700), (1, 17, 129, 8191),
-          (1, 31, 2049, 577), (20, 1025, 49, 48), (6, 2049, 33, 129), (70, 60, 65, 200), (2, 300, 200, 130), (1, 1100, 1000, 29), (5, 130, 257, 33), (1, 64, 64, 24575)]
+          (1, 31, 2049, 577), (20, 1025, 49, 48), (6, 2049, 33, 129), (70, 60, 65, 200), (80, 64, 64, 72), (70, 17, 136, 40), (2, 300, 200, 130), (1, 1100, 1000, 29), (5, 130, 257, 33), (1, 64, 64, 24575)]
 ROUTES = [("i8_direct", 127), ("f16_exact", 256), ("f16_exact", 1024), ("i8_karatsuba", 8000), ("i8_offset4", 32768)]
 
 
