@@ -247,14 +247,16 @@ qx_status plan_int_gemm(const GemmSpec& s, Plan* pl, uint64_t* ws_used) {
             // a short side (64x8192x8192 112 / 138, 48x6000x1000 17 / 21, 64 x
             // (130x64x512) 16 / 33, 300 x (64x64x1024) 48 / 129, 8 x
             // (8192x64x448) 44 / 53; longer sums 102x1960x2522 32 / 24, 22 x
-            // (96x80x1720) 32 / 27, 9 x (61x1899x7424) 473 / 328).
+            // (96x80x1720) 32 / 27, 8 x (38x2265x1482) 84 / 60, 7254x32x6542
+            // 102 / 90).
             if (route == R_F16_EXACT && f16_chunk(s.ba, s.bb) < 64 && feasible_i16(R_I8_KARATSUBA, s.ba, s.bb) &&
                 s.allow_nt && s.K >= 256 && use_i8nt(R_I8_KARATSUBA, s.M, s.N, s.K, s.batch) &&
                 (double)s.M * (double)s.N * (double)s.K * (double)s.batch >= (double)(1 << 28)) {
                 const int64_t Mp = pad_up(s.M, 64), Np = pad_up(s.N, 64), tiles = Mp / 64 * (Np / 64) * s.batch;
                 const bool sliced = dense_out(s) && reg_staged_ksplit(R_F16_EXACT, s.M, s.N, s.K, s.batch) > 1;
                 const bool short_side = Mp * Np <= 100 * (s.M + s.N) &&
-                                        (s.K <= (sliced ? 768 : 2048) || (sliced && s.batch == 1 && tiles >= 64));
+                                        (s.K <= (sliced ? 768 : 1024) ||
+                                         (sliced && s.batch == 1 && tiles >= 64 && std::min(s.M, s.N) > 32));
                 if (!short_side && !(sliced && tiles <= 16)) route = R_I8_KARATSUBA;
             }
         }
