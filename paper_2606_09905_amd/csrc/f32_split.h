@@ -2,9 +2,10 @@
 //
 // A float of 24 significant bits is the exact sum of three bf16 values,
 // x = h + m + l with |m| <= 2^-8 |x| and |l| <= 2^-17 |x| (each the rounding
-// of what the ones before it leave: the published three-term bf16 split).  Of
-// the nine products of two such sums all but l l are kept, which is at most
-// 2^-34 of the whole: a product is exact to a thousandth of fp32's rounding.
+// of what the ones before it leave: the three-term bf16 split of Henry, Tang
+// and Heinecke, 2019).  Of the nine products of two such sums all but l l are
+// kept, which is at most 2^-34 of the whole: a product is exact to a thousandth
+// of fp32's rounding.
 // Eight v_mfma_f32_32x32x16_bf16 (32 cycles each, 16 k) replace eight
 // v_mfma_f32_32x32x2f32 (64 cycles each).
 //
